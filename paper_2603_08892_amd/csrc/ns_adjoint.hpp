@@ -202,7 +202,8 @@ enum AdjOp {
   AOP_STORE = 0,  // out0 = V
   AOP_ACC = 1,    // out0 = in1 + V
   AOP_HEUN = 2,   // out0 = E_dt (in0 + in1) + V
-  AOP_EXACT = 3   // out0 = E_dt in0 + E_h in1 + V
+  AOP_EXACT = 3,  // out0 = E_dt in0 + E_h in1 + V
+  AOP_ANY = -1    // kernels only: the combination is an argument (AdjArgs::op)
 };
 
 template <typename R>
@@ -215,6 +216,7 @@ struct AdjArgs {
   int full;
   int ntzf;
   Lay lo0, li0, li1;  // layouts of out0, in0, in1
+  int op;             // the AdjOp of the AOP_ANY kernels
 };
 
 // Forward x pass of g1 = FFT(omega x lt) and g2 = FFT(lt x u):

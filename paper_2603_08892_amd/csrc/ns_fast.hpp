@@ -24,16 +24,19 @@
 
 namespace ns {
 
-constexpr int kFastL = 16;
-constexpr int kFastLp = kFastL + 1;
+// k_z columns of a tile of the strided passes: one 128-byte row of the scratch fields
+template <typename T>
+constexpr int tile_cols() { return 128 / (2 * (int)sizeof(T)); }
+constexpr int kFastL = tile_cols<float>();
 
 // Addressing: a block-uniform base pointer (a state component or scratch field)
 // plus a per-lane 32-bit element offset.  Every offset stays inside one component
-// of at most N^2 (N/2 + 1) elements, and the specialised sizes keep 8 bytes times
-// that below 2^32 (FastCfg checks it), so the byte offset fits 32 bits, the base
+// of at most N^2 (N/2 + 1) elements, and the specialised sizes keep the bytes of
+// that below 2^32 (LinePlan checks it), so the byte offset fits 32 bits, the base
 // stays in scalar registers and the index arithmetic is 32-bit.
-__device__ __forceinline__ Cx<float> ld_off(const Cx<float>* __restrict__ base, uint32_t off) {
-  return *reinterpret_cast<const Cx<float>*>(reinterpret_cast<const char*>(base) + off * 8u);
+template <typename T>
+__device__ __forceinline__ Cx<T> ld_off(const Cx<T>* __restrict__ base, uint32_t off) {
+  return *reinterpret_cast<const Cx<T>*>(reinterpret_cast<const char*>(base) + off * (uint32_t)sizeof(Cx<T>));
 }
 // STREAM: a non-temporal store, for the scratch fields and the compact stage
 // buffers of the grids whose step works on far more than the 256 MB last-level
@@ -44,15 +47,17 @@ __device__ __forceinline__ Cx<float> ld_off(const Cx<float>* __restrict__ base, 
 // was 5-17% slower.  Outputs in the
 // caller's layout (rows of N/2 + 1 elements, not whole 128-byte lines) take
 // plain stores: streamed partial lines made those passes 1.5 times slower.
-constexpr bool stream_stores(int n) { return n >= 240; }
-template <bool STREAM = false>
-__device__ __forceinline__ void st_off(Cx<float>* __restrict__ base, uint32_t off, Cx<float> v) {
+template <typename T>
+constexpr bool stream_stores(int n) { return (long long)n * n * n * (int)sizeof(Cx<T>) >= 8ll * 240 * 240 * 240; }
+template <bool STREAM = false, typename T>
+__device__ __forceinline__ void st_off(Cx<T>* __restrict__ base, uint32_t off, Cx<T> v) {
+  char* p = reinterpret_cast<char*>(base) + off * (uint32_t)sizeof(Cx<T>);
   if constexpr (STREAM) {
-    typedef float f2 __attribute__((ext_vector_type(2)));
-    const f2 w = {v.re, v.im};
-    __builtin_nontemporal_store(w, reinterpret_cast<f2*>(reinterpret_cast<char*>(base) + off * 8u));
+    typedef T v2 __attribute__((ext_vector_type(2)));
+    const v2 w = {v.re, v.im};
+    __builtin_nontemporal_store(w, reinterpret_cast<v2*>(p));
   } else {
-    *reinterpret_cast<Cx<float>*>(reinterpret_cast<char*>(base) + off * 8u) = v;
+    *reinterpret_cast<Cx<T>*>(p) = v;
   }
 }
 
@@ -61,9 +66,10 @@ __device__ __forceinline__ void st_off(Cx<float>* __restrict__ base, uint32_t of
 // values), so the load is unconditional and a thread issues all of its loads back
 // to back before the first use (a select would let the compiler turn the load
 // back into a branch with a wait right behind it).
-__device__ __forceinline__ Cx<float> ld_masked(const Cx<float>* __restrict__ base, uint32_t off, bool ok) {
-  const Cx<float> v = ld_off(base, ok ? off : 0u);
-  const float m = ok ? 1.f : 0.f;
+template <typename T>
+__device__ __forceinline__ Cx<T> ld_masked(const Cx<T>* __restrict__ base, uint32_t off, bool ok) {
+  const Cx<T> v = ld_off(base, ok ? off : 0u);
+  const T m = ok ? T(1) : T(0);
   return cx(v.re * m, v.im * m);
 }
 
@@ -90,22 +96,34 @@ __device__ __forceinline__ LineTest line_test(const Geom& g, int ky, int kz) {
   return L;
 }
 
-// Shift factors of the block's 16 k_z columns on row k_y (FP64, rounded once per
-// axis like phase1), computed by 16 threads into LDS.
-__device__ __forceinline__ void phase_cols(Cx<float>* phc, int ky, int kz0, const Shift& sh, int n, int tid) {
-  if (tid < kFastL) phc[tid] = cmul(phase1<float>(ky, sh.s[1], n), phase1<float>(kz0 + tid, sh.s[2], n));
+// Shift factors of the block's k_z columns on row k_y (FP64, rounded once per
+// axis like phase1), computed by one thread a column into LDS.
+template <typename T>
+__device__ __forceinline__ void phase_cols(Cx<T>* phc, int ky, int kz0, const Shift& sh, int n, int tid) {
+  if (tid < tile_cols<T>()) phc[tid] = cmul(phase1<T>(ky, sh.s[1], n), phase1<T>(kz0 + tid, sh.s[2], n));
 }
 
-// One line plan: N points over TPL threads, inverse and forward radix lists.
-template <int N_, int TPL_, typename Inv_, typename Fwd_>
-struct LinePlan {
+// One line plan: N points over TPL threads, inverse and forward radix lists;
+// LinePlan for FP32 fields, LinePlanD for FP64 ones.  L: columns of a tile, LP: its
+// pitch in LDS (one more, to spread the banks).
+template <typename T_, int N_, int TPL_, typename Inv_, typename Fwd_>
+struct TypedPlan {
+  using T = T_;
   static constexpr int N = N_;
   static constexpr int TPL = TPL_;
+  static constexpr int L = tile_cols<T>();
+  static constexpr int LP = L + 1;
+  static_assert((unsigned long long)sizeof(Cx<T>) * N * N * (N / 2 + 1) < (1ull << 32),
+                "32-bit byte offsets need sizeof(complex) N^2 (N/2+1) < 2^32");
   static constexpr int EPT = Inv_::template ept<N_, TPL_>();
   static_assert(EPT == Fwd_::template ept<N_, TPL_>(), "both directions hold the same registers");
   using Inv = Inv_;   // radices of the inverse transforms
   using Fwd = Fwd_;   // radices of the forward transforms (reverse order of Inv)
 };
+template <int N, int TPL, typename Inv, typename Fwd>
+struct LinePlan : TypedPlan<float, N, TPL, Inv, Fwd> {};
+template <int N, int TPL, typename Inv, typename Fwd>
+struct LinePlanD : TypedPlan<double, N, TPL, Inv, Fwd> {};
 
 // Plans of the five passes of one size; PZ = lines per block of the z pass; the
 // adjoint z pass (five inverse and three forward slices) may take its own plan ZA
@@ -116,8 +134,8 @@ template <typename XI, typename YP, typename ZP, int PZ_, typename XF, typename 
           bool YC_ = false>
 struct FastCfg {
   static constexpr int N = XI::N;
+  using T = typename XI::T;
   static constexpr bool YC = YC_;
-  static_assert(8ull * N * N * (N / 2 + 1) < (1ull << 32), "32-bit byte offsets need 8 N^2 (N/2+1) < 2^32");
   static constexpr int PZ = PZ_;
   static constexpr int PZA = PZA_;
   static_assert(N * N % PZ_ == 0 && N * N % PZA_ == 0, "the z passes run N^2 / P blocks of P whole lines");
@@ -142,33 +160,34 @@ struct FastCfg {
 // 3 alone; f_ycurl forms the vorticity from them as it loads them, so a tile
 // writes five fields here and is read as five there instead of six.
 template <typename C, bool CURL>
-__global__ void __launch_bounds__(kFastL * C::TPL)
-f_xinv(const Cx<float>* __restrict__ S, Lay ls, Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg,
+__global__ void __launch_bounds__(C::L * C::TPL)
+f_xinv(const Cx<typename C::T>* __restrict__ S, Lay ls, Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ twg,
         Shift sh, const int2* __restrict__ tiles, Geom g) {
+  using T = typename C::T;
   constexpr int N = C::N, TPL = C::TPL, EPT = C::EPT;
   using F = RegFft<N, TPL, +1, typename C::Inv>;
-  __shared__ Cx<float> tw[N];
-  __shared__ Cx<float> phx[N];
-  __shared__ Cx<float> phc[kFastL];
-  __shared__ Cx<float> xb[N * kFastLp];
+  __shared__ Cx<T> tw[N];
+  __shared__ Cx<T> phx[N];
+  __shared__ Cx<T> phc[C::L];
+  __shared__ Cx<T> xb[N * C::LP];
   const int tid = threadIdx.x;
-  const int l = tid % kFastL, t = tid / kFastL;
+  const int l = tid % C::L, t = tid / C::L;
   const int2 tile = tiles[blockIdx.x];
   const int yi = tile.x, kz0 = tile.y, kz = kz0 + l;
   const int ky = kval(yi, N);
-  for (int i = tid; i < N; i += kFastL * TPL) tw[i] = twg[i];
+  for (int i = tid; i < N; i += C::L * TPL) tw[i] = twg[i];
   const bool col = kz < g.kzn;
-  Cx<float> phyz = cx(1.f, 0.f);
+  Cx<T> phyz = cx(T(1), T(0));
   if (sh.on) {
-    phase_row(phx, N, sh.s[0], tid, kFastL * TPL);
+    phase_row(phx, N, sh.s[0], tid, C::L * TPL);
     phase_cols(phc, ky, kz0, sh, N, tid);
     __syncthreads();
     phyz = phc[l];
   }
-  const LineView<float, kFastLp> lv{xb + l};
+  const LineView<T, C::LP> lv{xb + l};
   const uint32_t sbase = (uint32_t)(yi * ls.pitch + kz0) + l, sstep = (uint32_t)(N * ls.pitch);
-  [[maybe_unused]] const float kyf = float(ky), kzf = float(kz);
-  Cx<float> ux[EPT], uy[EPT], uz[EPT], dy[EPT], dz[EPT];
+  [[maybe_unused]] const T kyf = T(ky), kzf = T(kz);
+  Cx<T> ux[EPT], uy[EPT], uz[EPT], dy[EPT], dz[EPT];
   {
     bool ok[EPT];
     uint32_t idx[EPT];
@@ -190,22 +209,22 @@ f_xinv(const Cx<float>* __restrict__ S, Lay ls, Cx<float>* __restrict__ W, const
   for (int i = 0; i < EPT; ++i) {
     const int p = F::in_at(t, i);
     if (sh.on) {
-      const Cx<float> phi = cmul(phx[p], phyz);
+      const Cx<T> phi = cmul(phx[p], phyz);
       ux[i] = cmul(ux[i], phi);
       uy[i] = cmul(uy[i], phi);
       uz[i] = cmul(uz[i], phi);
     }
-    const float kxf = float(kval(p, N));
+    const T kxf = T(kval(p, N));
     dy[i] = mul_i(scale(uy[i], kxf));
     dz[i] = mul_i(scale(uz[i], kxf));
   }
   const uint32_t obase = (uint32_t)(yi * g.kzp + kz0) + l, ostep = (uint32_t)(N * g.kzp);
-  auto store = [&](int f, const Cx<float>* v) {
+  auto store = [&](int f, const Cx<T>* v) {
     if (col) {
 #pragma unroll
       for (int i = 0; i < EPT; ++i)
         if (F::out_ok(t, i))
-          st_off<stream_stores(N)>(W + f * g.wcomp, (uint32_t)F::out_pos(t, i) * ostep + obase, v[i]);
+          st_off<stream_stores<T>(N)>(W + f * g.wcomp, (uint32_t)F::out_pos(t, i) * ostep + obase, v[i]);
     }
   };
   F::run(uy, t, lv, tw);
@@ -235,25 +254,26 @@ f_xinv(const Cx<float>* __restrict__ S, Lay ls, Cx<float>* __restrict__ W, const
 
 // ------------------------------------------------------------------ y passes (in place)
 template <typename C, int S>
-__global__ void __launch_bounds__(kFastL * C::TPL)
-f_ypass(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, int ntz, Geom g) {
+__global__ void __launch_bounds__(C::L * C::TPL)
+f_ypass(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ twg, int ntz, Geom g) {
+  using T = typename C::T;
   constexpr int N = C::N, TPL = C::TPL, EPT = C::EPT;
   using F = RegFft<N, TPL, S, std::conditional_t<(S > 0), typename C::Inv, typename C::Fwd>>;
-  __shared__ Cx<float> tw[N];
-  __shared__ Cx<float> xb[N * kFastLp];
+  __shared__ Cx<T> tw[N];
+  __shared__ Cx<T> xb[N * C::LP];
   const int tid = threadIdx.x;
-  const int l = tid % kFastL, t = tid / kFastL;
+  const int l = tid % C::L, t = tid / C::L;
   const int b = blockIdx.x;
   const int kzt = b % ntz, rest = b / ntz;
   const int x = rest % N, f = rest / N;
-  const int kz0 = kzt * kFastL, kz = kz0 + l;
+  const int kz0 = kzt * C::L, kz = kz0 + l;
   const int yb = ybound(g, kz0);
-  for (int i = tid; i < N; i += kFastL * TPL) tw[i] = twg[i];
+  for (int i = tid; i < N; i += C::L * TPL) tw[i] = twg[i];
   const bool col = kz < g.kzn;
-  Cx<float>* base = W + f * g.wcomp;
+  Cx<T>* base = W + f * g.wcomp;
   const uint32_t rbase = (uint32_t)(x * N * g.kzp + kz0) + l;
-  const LineView<float, kFastLp> lv{xb + l};
-  Cx<float> v[EPT];
+  const LineView<T, C::LP> lv{xb + l};
+  Cx<T> v[EPT];
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
     const int p = F::in_at(t, i);
@@ -265,7 +285,7 @@ f_ypass(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, int ntz, G
     for (int i = 0; i < EPT; ++i) {
       const int p = F::out_pos(t, i);
       if (F::out_ok(t, i) && (S > 0 || abs(kval(p, N)) <= yb))
-        st_off<stream_stores(N)>(base, (uint32_t)(p * g.kzp) + rbase, v[i]);
+        st_off<stream_stores<T>(N)>(base, (uint32_t)(p * g.kzp) + rbase, v[i]);
     }
   }
 }
@@ -285,27 +305,28 @@ f_ypass(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, int ntz, G
 // 32 threads a line this allows one block per CU, where the six single-field
 // blocks of f_ypass keep two or three resident and are faster.
 template <typename C>
-__global__ void __launch_bounds__(kFastL * C::TPL)
-f_ycurl(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, int ntz, Geom g) {
+__global__ void __launch_bounds__(C::L * C::TPL)
+f_ycurl(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ twg, int ntz, Geom g) {
+  using T = typename C::T;
   constexpr int N = C::N, TPL = C::TPL, EPT = C::EPT;
   using F = RegFft<N, TPL, +1, typename C::Inv>;
-  __shared__ Cx<float> tw[N];
-  __shared__ Cx<float> xb[N * kFastLp];
+  __shared__ Cx<T> tw[N];
+  __shared__ Cx<T> xb[N * C::LP];
   const int tid = threadIdx.x;
-  const int l = tid % kFastL, t = tid / kFastL;
+  const int l = tid % C::L, t = tid / C::L;
   const int b = blockIdx.x;
   const int kzt = b % ntz, rest = b / ntz;
   const int x = rest % N, grp = rest / N;
-  const int kz0 = kzt * kFastL, kz = kz0 + l;
+  const int kz0 = kzt * C::L, kz = kz0 + l;
   const int yb = ybound(g, kz0);
-  for (int i = tid; i < N; i += kFastL * TPL) tw[i] = twg[i];
+  for (int i = tid; i < N; i += C::L * TPL) tw[i] = twg[i];
   const bool col = kz < g.kzn;
-  Cx<float>* const Wa = W + (grp ? 0 : 1) * g.wcomp;
-  Cx<float>* const Wb = W + (grp ? 4 : 2) * g.wcomp;
-  Cx<float>* const Wc = W + (grp ? 5 : 3) * g.wcomp;
+  Cx<T>* const Wa = W + (grp ? 0 : 1) * g.wcomp;
+  Cx<T>* const Wb = W + (grp ? 4 : 2) * g.wcomp;
+  Cx<T>* const Wc = W + (grp ? 5 : 3) * g.wcomp;
   const uint32_t rbase = (uint32_t)(x * N * g.kzp + kz0) + l;
-  const LineView<float, kFastLp> lv{xb + l};
-  Cx<float> va[EPT], vb[EPT], vc[EPT];
+  const LineView<T, C::LP> lv{xb + l};
+  Cx<T> va[EPT], vb[EPT], vc[EPT];
   {
     bool ok[EPT];
     uint32_t idx[EPT];
@@ -325,26 +346,26 @@ f_ycurl(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, int ntz, G
       for (int i = 0; i < EPT; ++i) vc[i] = ld_masked(Wc, idx[i], ok[i]);
     }
   }
-  const float kzf = float(kz);
+  const T kzf = T(kz);
   if (grp) {
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
-      const float kyf = float(kval(F::in_at(t, i), N));
+      const T kyf = T(kval(F::in_at(t, i), N));
       vb[i] = mul_i(scale(va[i], kzf)) - vb[i];  // omega_y
       vc[i] = vc[i] - mul_i(scale(va[i], kyf));  // omega_z
     }
   } else {
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
-      const float kyf = float(kval(F::in_at(t, i), N));
+      const T kyf = T(kval(F::in_at(t, i), N));
       vc[i] = mul_i(scale(vb[i], kyf) - scale(va[i], kzf));  // omega_x
     }
   }
-  auto store = [&](Cx<float>* base, const Cx<float>* v) {
+  auto store = [&](Cx<T>* base, const Cx<T>* v) {
     if (col) {
 #pragma unroll
       for (int i = 0; i < EPT; ++i)
-        if (F::out_ok(t, i)) st_off<stream_stores(N)>(base, (uint32_t)(F::out_pos(t, i) * g.kzp) + rbase, v[i]);
+        if (F::out_ok(t, i)) st_off<stream_stores<T>(N)>(base, (uint32_t)(F::out_pos(t, i) * g.kzp) + rbase, v[i]);
     }
   };
   F::run(va, t, lv, tw);
@@ -363,15 +384,16 @@ f_ycurl(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, int ntz, G
 // spectra are split through LDS.  Output scratch fields 0, 1, 2 = f_x, f_y, f_z (unnormalised).
 template <typename C, int P>
 __global__ void __launch_bounds__(P * C::TPL)
-f_zcross(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Geom g) {
+f_zcross(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ twg, Geom g) {
+  using T = typename C::T;
   constexpr int N = C::N, TPL = C::TPL, EPT = C::EPT, HN = N / 2, NT = P * TPL;
   using FI = RegFft<N, TPL, +1, typename C::Inv>;
   using FF = RegFft<N, TPL, -1, typename C::Fwd>;
   static_assert(FI::RL == FF::R0, "the forward transform must start with the last inverse radix");
   constexpr int LP = line_pitch(N);
-  __shared__ Cx<float> tw[N];
-  __shared__ Cx<float> xb[P * LP];  // exchanges, then the spectrum of f_z
-  __shared__ Cx<float> sp[P * N];   // spectrum of f_x + i f_y
+  __shared__ Cx<T> tw[N];
+  __shared__ Cx<T> xb[P * LP];  // exchanges, then the spectrum of f_z
+  __shared__ Cx<T> sp[P * N];   // spectrum of f_x + i f_y
   const int tid = threadIdx.x;
   const int p = tid / TPL, t = tid % TPL;
   // a line's threads within one wavefront synchronise at wavefront scope; a line
@@ -380,16 +402,16 @@ f_zcross(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Geom g) {
   const uint32_t line0 = (uint32_t)blockIdx.x * P;
   for (int i = tid; i < N; i += NT) tw[i] = twg[i];
   __syncthreads();  // the line transforms below synchronise only within a wavefront
-  const LineView<float, 1> lv{xb + p * LP};
+  const LineView<T, 1> lv{xb + p * LP};
   const uint32_t lbase = (line0 + p) * (uint32_t)g.kzp;
-  float fx[EPT], fy[EPT], fz[EPT];
-  Cx<float> z[2][EPT];
-  Cx<float> v[EPT];
+  T fx[EPT], fy[EPT], fz[EPT];
+  Cx<T> z[2][EPT];
+  Cx<T> v[EPT];
   // raw half-spectrum pairs of the slices, loaded two slices ahead so that the
   // loads overlap the transforms (the barriers inside a transform keep the
   // compiler from moving later loads above it)
-  Cx<float> ra[2][EPT], rb[2][EPT];
-  auto fetch = [&](int q, Cx<float>* a, Cx<float>* b) {
+  Cx<T> ra[2][EPT], rb[2][EPT];
+  auto fetch = [&](int q, Cx<T>* a, Cx<T>* b) {
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
       const int pos = FI::in_at(t, i);
@@ -405,7 +427,7 @@ f_zcross(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Geom g) {
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
       const int pos = FI::in_at(t, i);
-      const Cx<float> a = ra[q & 1][i], bb = rb[q & 1][i];
+      const Cx<T> a = ra[q & 1][i], bb = rb[q & 1][i];
       if (pos == 0 || pos == HN) v[i] = cx(a.re, bb.re);
       else if (pos < HN) v[i] = cx(a.re - bb.im, a.im + bb.re);
       else v[i] = cx(a.re + bb.im, bb.re - a.im);
@@ -419,8 +441,8 @@ f_zcross(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Geom g) {
   }
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
-    const float ux = z[0][i].re, uy = z[0][i].im, uz = z[1][i].re, wx = z[1][i].im;
-    const float wy = v[i].re, wz = v[i].im;
+    const T ux = z[0][i].re, uy = z[0][i].im, uz = z[1][i].re, wx = z[1][i].im;
+    const T wy = v[i].re, wz = v[i].im;
     fx[i] = uy * wz - uz * wy;
     fy[i] = uz * wx - ux * wz;
     fz[i] = ux * wy - uy * wx;
@@ -432,7 +454,7 @@ f_zcross(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Geom g) {
   for (int i = 0; i < EPT; ++i)
     if (FF::out_ok(t, i)) sp[p * N + FF::out_pos(t, i)] = v[i];
 #pragma unroll
-  for (int i = 0; i < EPT; ++i) v[i] = cx(fz[i], 0.f);
+  for (int i = 0; i < EPT; ++i) v[i] = cx(fz[i], T(0));
   FF::template run<WV>(v, t, lv, tw);
   __syncthreads();
 #pragma unroll
@@ -441,11 +463,11 @@ f_zcross(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Geom g) {
   __syncthreads();
   for (int idx = tid; idx < P * g.kzn; idx += NT) {
     const int k = idx % g.kzn, pp = idx / g.kzn;
-    const Cx<float> c1 = sp[pp * N + k], c2 = sp[pp * N + ((N - k) % N)];
+    const Cx<T> c1 = sp[pp * N + k], c2 = sp[pp * N + ((N - k) % N)];
     const uint32_t off = (line0 + pp) * (uint32_t)g.kzp + k;
-    st_off<stream_stores(N)>(W, off, cx(0.5f * (c1.re + c2.re), 0.5f * (c1.im - c2.im)));
-    st_off<stream_stores(N)>(W + g.wcomp, off, cx(0.5f * (c1.im + c2.im), -0.5f * (c1.re - c2.re)));
-    st_off<stream_stores(N)>(W + 2 * g.wcomp, off, xb[pp * LP + k]);
+    st_off<stream_stores<T>(N)>(W, off, cx(T(0.5) * (c1.re + c2.re), T(0.5) * (c1.im - c2.im)));
+    st_off<stream_stores<T>(N)>(W + g.wcomp, off, cx(T(0.5) * (c1.im + c2.im), T(-0.5) * (c1.re - c2.re)));
+    st_off<stream_stores<T>(N)>(W + 2 * g.wcomp, off, xb[pp * LP + k]);
   }
 }
 
@@ -457,26 +479,29 @@ f_zcross(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Geom g) {
 // transform's last), so the tile is not read back.  An out1 that only feeds the
 // next evaluation is not stored.  FEED needs a.full == 0 (the blocks are then the
 // active tiles, the same as the x-inverse pass); CURL as in f_xinv.
+// OP_ANY, FEED_ANY: the stage operation and the fed output come from the arguments
+// (block-uniform branches), one kernel for every stage.
 template <typename C, int OP, int FEED, bool CURL>
-__global__ void __launch_bounds__(kFastL * C::TPL)
-f_xfwd(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Shift sh, Shift sh2,
-       const int2* __restrict__ tiles, Geom g, EpiArgs<float> a) {
+__global__ void __launch_bounds__(C::L * C::TPL)
+f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ twg, Shift sh, Shift sh2,
+       const int2* __restrict__ tiles, Geom g, EpiArgs<typename C::T> a) {
+  using T = typename C::T;
   constexpr int N = C::N, TPL = C::TPL, EPT = C::EPT;
   using F = RegFft<N, TPL, -1, typename C::Fwd>;
   using FI = RegFft<N, TPL, +1, typename C::Inv>;
   static_assert(FEED == 0 || F::RL == FI::R0, "the inverse transform must start with the forward's last radix");
-  __shared__ Cx<float> tw[N];
-  __shared__ Cx<float> phx[N];
-  __shared__ Cx<float> phc[kFastL];
-  __shared__ Cx<float> phx2[FEED ? N : 1];
-  __shared__ Cx<float> phc2[FEED ? kFastL : 1];
-  __shared__ Cx<float> xb[N * kFastLp];
+  __shared__ Cx<T> tw[N];
+  __shared__ Cx<T> phx[N];
+  __shared__ Cx<T> phc[C::L];
+  __shared__ Cx<T> phx2[FEED ? N : 1];
+  __shared__ Cx<T> phc2[FEED ? C::L : 1];
+  __shared__ Cx<T> xb[N * C::LP];
   const int tid = threadIdx.x;
-  const int l = tid % kFastL, t = tid / kFastL;
+  const int l = tid % C::L, t = tid / C::L;
   int yi, kz0;
   if (a.full) {
     yi = blockIdx.x / a.ntzf;
-    kz0 = (blockIdx.x % a.ntzf) * kFastL;
+    kz0 = (blockIdx.x % a.ntzf) * C::L;
   } else {
     const int2 tile = tiles[blockIdx.x];
     yi = tile.x;
@@ -485,64 +510,67 @@ f_xfwd(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Shift sh, S
   const int kz = kz0 + l;
   const int ky = kval(yi, N);
   const bool active = line_active(g, ky, kz0);
-  const LineView<float, kFastLp> lv{xb + l};
-  Cx<float> r[3][EPT];
-  Cx<float> phyz = cx(1.f, 0.f);
+  const LineView<T, C::LP> lv{xb + l};
+  Cx<T> r[3][EPT];
+  Cx<T> phyz = cx(T(1), T(0));
   // stage operands, read per chunk of points before that chunk's stores (out0 may
   // alias an operand, which keeps the compiler from hoisting loads above stores):
   // half of the points per chunk for two-operand stages, and for one-operand
   // stages at N <= 128 (fewer registers, four waves per SIMD instead of three;
   // measured faster there, slower at N = 256); the first chunk is read before the
   // last transform so that its latency overlaps it
-  constexpr bool need0 = (OP == OP_HEUN1 || OP == OP_EX1B || OP == OP_EX2B || OP == OP_RK4_0 ||
-                          OP == OP_RK4_1 || OP == OP_RK4_2 || OP == OP_MID1 || OP == OP_MID2 ||
-                          OP == OP_EUL || OP == OP_EULAV);
-  constexpr bool need1 = (OP == OP_AVG || OP == OP_HEUN2 || OP == OP_EX1B || OP == OP_EX2B ||
-                          OP == OP_RK4_1 || OP == OP_RK4_2 || OP == OP_RK4_3 || OP == OP_ACC ||
-                          OP == OP_EULAV);
-  constexpr bool use1 = (OP == OP_HEUN1 || OP == OP_RK4_0 || OP == OP_RK4_1 || OP == OP_RK4_2) && FEED != 2;
-  static_assert(FEED == 0 || op_can_feed(OP, FEED), "this stage output is not an evaluation input");
-  Cx<float> nx[FEED ? 3 : 1][FEED ? EPT : 1];  // the fed output on this thread's points
+  const int op = OP == OP_ANY ? a.op : OP;
+  [[maybe_unused]] const int feed = FEED == FEED_ANY ? a.feed : FEED;
+  constexpr bool may0 = OP == OP_ANY || op_reads0(OP), may1 = OP == OP_ANY || op_reads1(OP);
+  const bool need0 = op_reads0(op), need1 = op_reads1(op);
+  constexpr bool may_out1 = (OP == OP_ANY || op_writes1(OP)) && FEED != 2;
+  const bool use1 = may_out1 && op_writes1(op) && feed != 2;
+  static_assert(FEED == 0 || FEED == FEED_ANY || op_can_feed(OP, FEED), "this stage output is not an evaluation input");
+  Cx<T> nx[FEED ? 3 : 1][FEED ? EPT : 1];  // the fed output on this thread's points
   if constexpr (FEED != 0) {
 #pragma unroll
     for (int c = 0; c < 3; ++c)
 #pragma unroll
-      for (int i = 0; i < EPT; ++i) nx[c][i] = cx(0.f, 0.f);
+      for (int i = 0; i < EPT; ++i) nx[c][i] = cx(T(0), T(0));
   }
-  constexpr int CH = ((need0 && need1) || ((need0 || need1) && N <= 128)) ? (EPT + 1) / 2 : EPT;
+  constexpr int CH = ((may0 && may1) || ((may0 || may1) && N <= 128)) ? (EPT + 1) / 2 : EPT;
   const LineTest keep = line_test(g, ky, kz);
   const bool line_kept = active && kz < g.kzn;
   // streaming stores into the compact stage buffers only (rows of whole 128-byte lines)
-  const bool st0 = stream_stores(N) && a.lo0.pitch == g.kzp;
-  [[maybe_unused]] const bool st1 = stream_stores(N) && a.lo1.pitch == g.kzp;
-  Cx<float> s0v[need0 ? 3 : 1][need0 ? CH : 1], s1v[need1 ? 3 : 1][need1 ? CH : 1];
+  const bool st0 = stream_stores<T>(N) && a.lo0.pitch == g.kzp;
+  [[maybe_unused]] const bool st1 = stream_stores<T>(N) && a.lo1.pitch == g.kzp;
+  Cx<T> s0v[may0 ? 3 : 1][may0 ? CH : 1], s1v[may1 ? 3 : 1][may1 ? CH : 1];
   auto load_ops = [&](int c0) {
 #pragma unroll
     for (int j = 0; j < CH; ++j) {
       if (c0 + j >= EPT) break;  // an odd register count: the second chunk is one short
       const int p = F::out_at(t, c0 + j);
       const bool ok = line_kept && F::out_ok(t, c0 + j) && keep(kval(p, N));
-      if constexpr (need0) {
+      if constexpr (may0) {
         const uint32_t ii0 = (uint32_t)((p * N + yi) * a.li0.pitch + kz);
+        if (need0) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) s0v[c][j] = ld_masked(a.in0 + c * a.li0.cs, ii0, ok);
+          for (int c = 0; c < 3; ++c) s0v[c][j] = ld_masked(a.in0 + c * a.li0.cs, ii0, ok);
+        }
       }
-      if constexpr (need1) {
+      if constexpr (may1) {
         const uint32_t ii1 = (uint32_t)((p * N + yi) * a.li1.pitch + kz);
+        if (need1) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) s1v[c][j] = ld_masked(a.in1 + c * a.li1.cs, ii1, ok);
+          for (int c = 0; c < 3; ++c) s1v[c][j] = ld_masked(a.in1 + c * a.li1.cs, ii1, ok);
+        }
       }
     }
   };
   if (active) {
-    for (int i = tid; i < N; i += kFastL * TPL) tw[i] = twg[i];
+    for (int i = tid; i < N; i += C::L * TPL) tw[i] = twg[i];
     if (sh.on) {
-      phase_row(phx, N, sh.s[0], tid, kFastL * TPL);
+      phase_row(phx, N, sh.s[0], tid, C::L * TPL);
       phase_cols(phc, ky, kz0, sh, N, tid);
     }
     if constexpr (FEED != 0) {
       if (sh2.on) {
-        phase_row(phx2, N, sh2.s[0], tid, kFastL * TPL);
+        phase_row(phx2, N, sh2.s[0], tid, C::L * TPL);
         phase_cols(phc2, ky, kz0, sh2, N, tid);
       }
     }
@@ -566,7 +594,7 @@ f_xfwd(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Shift sh, S
   }
   const bool epi_on = !(kz >= g.h || (!a.full && kz >= g.kzn));
   if (FEED == 0 && !epi_on) return;
-  const float inv_n3 = 1.f / (float(N) * float(N) * float(N));
+  const T inv_n3 = T(1) / (T(N) * T(N) * T(N));
   if (epi_on) {
 #pragma unroll
   for (int c0 = 0; c0 < EPT; c0 += CH) {
@@ -583,87 +611,88 @@ f_xfwd(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Shift sh, S
       // outside the retained set: zero in outputs that must be complete (full
       // mode, the caller's arrays); stage buffers are only read at retained modes
       if (a.full)
-        for (int c = 0; c < 3; ++c) st_off(a.out0 + c * a.lo0.cs, io0, cx(0.f, 0.f));
+        for (int c = 0; c < 3; ++c) st_off(a.out0 + c * a.lo0.cs, io0, cx(T(0), T(0)));
       continue;
     }
     const uint32_t io1 = use1 ? (uint32_t)((p * N + yi) * a.lo1.pitch + kz) : 0u;
-    Cx<float> Fv[3] = {scale(r[0][i], inv_n3), scale(r[1][i], inv_n3), scale(r[2][i], inv_n3)};
+    Cx<T> Fv[3] = {scale(r[0][i], inv_n3), scale(r[1][i], inv_n3), scale(r[2][i], inv_n3)};
     if (sh.on) {
-      const Cx<float> phi = cmul(phx[p], phyz);
+      const Cx<T> phi = cmul(phx[p], phyz);
       Fv[0] = cmulc(Fv[0], phi);
       Fv[1] = cmulc(Fv[1], phi);
       Fv[2] = cmulc(Fv[2], phi);
     }
     const int k2 = kx * kx + ky * ky + kz * kz;
     if (k2 == 0) {
-      Fv[0] = Fv[1] = Fv[2] = cx(0.f, 0.f);
+      Fv[0] = Fv[1] = Fv[2] = cx(T(0), T(0));
     } else {
-      const float rk2 = 1.f / float(k2);
-      const float kxr = float(kx), kyr = float(ky), kzr = float(kz);
-      const Cx<float> kd = scale(scale(Fv[0], kxr) + scale(Fv[1], kyr) + scale(Fv[2], kzr), rk2);
+      const T rk2 = T(1) / T(k2);
+      const T kxr = T(kx), kyr = T(ky), kzr = T(kz);
+      const Cx<T> kd = scale(scale(Fv[0], kxr) + scale(Fv[1], kyr) + scale(Fv[2], kzr), rk2);
       Fv[0] = Fv[0] - scale(kd, kxr);
       Fv[1] = Fv[1] - scale(kd, kyr);
       Fv[2] = Fv[2] - scale(kd, kzr);
     }
-    float eh = 1.f, edt = 1.f;
-    if (op_uses_etab(OP)) { eh = a.eh[k2]; edt = a.edt[k2]; }
-    const float dt = a.dt;
+    T eh = T(1), edt = T(1);
+    if (op_uses_etab(op)) { eh = a.eh[k2]; edt = a.edt[k2]; }
+    const T dt = a.dt;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      Cx<float>* out0 = a.out0 + c * a.lo0.cs;
-      Cx<float>* out1 = use1 ? a.out1 + c * a.lo1.cs : nullptr;
-      Cx<float> Nv = Fv[c];
-      Cx<float> O = cx(0.f, 0.f);
-      if (op_forced(OP) && a.force != nullptr && k2 >= 4 && k2 <= 9)
+      Cx<T>* out0 = a.out0 + c * a.lo0.cs;
+      Cx<T>* out1 = use1 ? a.out1 + c * a.lo1.cs : nullptr;
+      Cx<T> Nv = Fv[c];
+      Cx<T> O = cx(T(0), T(0));
+      if (op_forced(op) && a.force != nullptr && k2 >= 4 && k2 <= 9)
         O = a.force[c * 196 + ((kx + 3) * 7 + (ky + 3)) * 4 + kz];
-      if (OP != OP_HEUN1) Nv = Nv + O;  // RK4 slopes N + O (zero for the other ops)
-      Cx<float> s0 = cx(0.f, 0.f), s1 = cx(0.f, 0.f);
-      if constexpr (need0) s0 = s0v[c][j];
-      if constexpr (need1) s1 = s1v[c][j];
-      Cx<float> v0 = cx(0.f, 0.f), v1 = cx(0.f, 0.f);
-      if (OP == OP_STORE) {
+      if (op != OP_HEUN1) Nv = Nv + O;  // RK4 slopes N + O (zero for the other ops)
+      Cx<T> s0 = cx(T(0), T(0)), s1 = cx(T(0), T(0));
+      if constexpr (may0) s0 = s0v[c][j];
+      if constexpr (may1) s1 = s1v[c][j];
+      Cx<T> v0 = cx(T(0), T(0)), v1 = cx(T(0), T(0));
+      if (op == OP_STORE) {
         v0 = Nv;
-      } else if (OP == OP_AVG) {
-        v0 = scale(s1 + Nv, 0.5f);
-      } else if (OP == OP_HEUN1) {
+      } else if (op == OP_AVG) {
+        v0 = scale(s1 + Nv, T(0.5));
+      } else if (op == OP_HEUN1) {
         v1 = scale(s0 + scale(Nv + O, dt), edt);
-        v0 = scale(s0, edt) + scale(Nv + O + O, 0.5f * dt * eh);
-      } else if (OP == OP_HEUN2) {
-        v0 = s1 + scale(Nv, 0.5f * dt * eh);
-      } else if (OP == OP_EX1B) {
-        v0 = scale(s0 + scale(s1 + Nv, 0.5f * dt * a.w), eh);
-      } else if (OP == OP_EX2B) {
+        v0 = scale(s0, edt) + scale(Nv + O + O, T(0.5) * dt * eh);
+      } else if (op == OP_HEUN2) {
+        v0 = s1 + scale(Nv, T(0.5) * dt * eh);
+      } else if (op == OP_EX1B) {
+        v0 = scale(s0 + scale(s1 + Nv, T(0.5) * dt * a.w), eh);
+      } else if (op == OP_EX2B) {
         v0 = scale(s0, edt) + scale(s1 + Nv, dt * a.w * eh);
-      } else if (OP == OP_RK4_0) {
-        v1 = scale(s0 + scale(Nv, 0.5f * dt), eh);
-        v0 = scale(s0 + scale(Nv, dt / 6.f), edt);
-      } else if (OP == OP_RK4_1) {
-        v1 = scale(s0, eh) + scale(Nv, 0.5f * dt);
-        v0 = s1 + scale(Nv, dt / 3.f * eh);
-      } else if (OP == OP_RK4_2) {
+      } else if (op == OP_RK4_0) {
+        v1 = scale(s0 + scale(Nv, T(0.5) * dt), eh);
+        v0 = scale(s0 + scale(Nv, dt / T(6)), edt);
+      } else if (op == OP_RK4_1) {
+        v1 = scale(s0, eh) + scale(Nv, T(0.5) * dt);
+        v0 = s1 + scale(Nv, dt / T(3) * eh);
+      } else if (op == OP_RK4_2) {
         v1 = scale(s0, edt) + scale(Nv, dt * eh);
-        v0 = s1 + scale(Nv, dt / 3.f * eh);
-      } else if (OP == OP_RK4_3) {
-        v0 = s1 + scale(Nv, dt / 6.f);
-      } else if (OP == OP_ACC) {
+        v0 = s1 + scale(Nv, dt / T(3) * eh);
+      } else if (op == OP_RK4_3) {
+        v0 = s1 + scale(Nv, dt / T(6));
+      } else if (op == OP_ACC) {
         v0 = s1 + Nv;
-      } else if (OP == OP_MID1) {
-        v0 = scale(s0 + scale(Nv, 0.5f * dt), eh);
-      } else if (OP == OP_MID2) {
+      } else if (op == OP_MID1) {
+        v0 = scale(s0 + scale(Nv, T(0.5) * dt), eh);
+      } else if (op == OP_MID2) {
         v0 = scale(s0, edt) + scale(Nv, dt * eh);
-      } else if (OP == OP_EUL) {
+      } else if (op == OP_EUL) {
         v0 = scale(s0 + scale(Nv, dt), edt);
       } else {  // OP_EULAV
         v0 = scale(s0 + scale(s1 + Nv, dt * a.w), edt);
       }
-      if constexpr (use1) {
-        if (st1) st_off<true>(out1, io1, v1);
-        else st_off(out1, io1, v1);
+      if constexpr (may_out1) {
+        if (use1) {
+          if (st1) st_off<true>(out1, io1, v1);
+          else st_off(out1, io1, v1);
+        }
       }
       if (st0) st_off<true>(out0, io0, v0);
       else st_off(out0, io0, v0);
-      if constexpr (FEED == 1) nx[c][i] = v0;
-      if constexpr (FEED == 2) nx[c][i] = v1;
+      if constexpr (FEED != 0) nx[c][i] = feed == 1 ? v0 : v1;
     }
   }
   }
@@ -671,9 +700,9 @@ f_xfwd(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Shift sh, S
   if constexpr (FEED != 0) {
     // the next evaluation's x-inverse pass on this tile (as f_xinv<C, CURL>, from registers)
     const bool col = kz < g.kzn;
-    Cx<float> ux[EPT], uy[EPT], uz[EPT], dy[EPT], dz[EPT];
-    [[maybe_unused]] const float kyf = float(ky), kzf = float(kz);
-    const Cx<float> phyz2 = sh2.on ? phc2[l] : cx(1.f, 0.f);
+    Cx<T> ux[EPT], uy[EPT], uz[EPT], dy[EPT], dz[EPT];
+    [[maybe_unused]] const T kyf = T(ky), kzf = T(kz);
+    const Cx<T> phyz2 = sh2.on ? phc2[l] : cx(T(1), T(0));
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
       const int p = FI::in_at(t, i);
@@ -681,22 +710,22 @@ f_xfwd(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Shift sh, S
       uy[i] = nx[1][i];
       uz[i] = nx[2][i];
       if (sh2.on) {
-        const Cx<float> phi = cmul(phx2[p], phyz2);
+        const Cx<T> phi = cmul(phx2[p], phyz2);
         ux[i] = cmul(ux[i], phi);
         uy[i] = cmul(uy[i], phi);
         uz[i] = cmul(uz[i], phi);
       }
-      const float kxf = float(kval(p, N));
+      const T kxf = T(kval(p, N));
       dy[i] = mul_i(scale(uy[i], kxf));
       dz[i] = mul_i(scale(uz[i], kxf));
     }
     const uint32_t obase = (uint32_t)(yi * g.kzp + kz0) + l, ostep = (uint32_t)(N * g.kzp);
-    auto store = [&](int f, const Cx<float>* v) {
+    auto store = [&](int f, const Cx<T>* v) {
       if (col) {
 #pragma unroll
         for (int i = 0; i < EPT; ++i)
           if (FI::out_ok(t, i))
-            st_off<stream_stores(N)>(W + f * g.wcomp, (uint32_t)FI::out_pos(t, i) * ostep + obase, v[i]);
+            st_off<stream_stores<T>(N)>(W + f * g.wcomp, (uint32_t)FI::out_pos(t, i) * ostep + obase, v[i]);
       }
     };
     FI::run(uy, t, lv, tw);

@@ -17,60 +17,61 @@ namespace ns {
 // lam_in = cA E_A(k) A + cB E_B(k) B on the retained modes, projected and shifted,
 // inverse x transforms into scratch fields 6, 7, 8 (tiles as f_xinv).
 template <typename C>
-__global__ void __launch_bounds__(kFastL * C::TPL)
-f_xlam(LamArgs<float> la, Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Shift sh,
+__global__ void __launch_bounds__(C::L * C::TPL)
+f_xlam(LamArgs<typename C::T> la, Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ twg, Shift sh,
        const int2* __restrict__ tiles, Geom g) {
+  using T = typename C::T;
   constexpr int N = C::N, TPL = C::TPL, EPT = C::EPT;
   using F = RegFft<N, TPL, +1, typename C::Inv>;
-  __shared__ Cx<float> tw[N];
-  __shared__ Cx<float> phx[N];
-  __shared__ Cx<float> phc[kFastL];
-  __shared__ Cx<float> xb[N * kFastLp];
+  __shared__ Cx<T> tw[N];
+  __shared__ Cx<T> phx[N];
+  __shared__ Cx<T> phc[C::L];
+  __shared__ Cx<T> xb[N * C::LP];
   const int tid = threadIdx.x;
-  const int l = tid % kFastL, t = tid / kFastL;
+  const int l = tid % C::L, t = tid / C::L;
   const int2 tile = tiles[blockIdx.x];
   const int yi = tile.x, kz0 = tile.y, kz = kz0 + l;
   const int ky = kval(yi, N);
-  for (int i = tid; i < N; i += kFastL * TPL) tw[i] = twg[i];
-  Cx<float> phyz = cx(1.f, 0.f);
+  for (int i = tid; i < N; i += C::L * TPL) tw[i] = twg[i];
+  Cx<T> phyz = cx(T(1), T(0));
   if (sh.on) {
-    phase_row(phx, N, sh.s[0], tid, kFastL * TPL);
+    phase_row(phx, N, sh.s[0], tid, C::L * TPL);
     phase_cols(phc, ky, kz0, sh, N, tid);
     __syncthreads();
     phyz = phc[l];
   }
   const bool col = kz < g.kzn;
   const LineTest keep = line_test(g, ky, kz);
-  const LineView<float, kFastLp> lv{xb + l};
-  Cx<float> q[3][EPT];
+  const LineView<T, C::LP> lv{xb + l};
+  Cx<T> q[3][EPT];
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
     const int p = F::in_at(t, i);
     const int kx = kval(p, N);
     const bool ok = col && F::in_ok(t, i) && keep(kx);
     const int k2 = ok ? kx * kx + ky * ky + kz * kz : 0;
-    const float fa = la.cA * (la.eA ? la.eA[k2] : 1.f);
+    const T fa = la.cA * (la.eA ? la.eA[k2] : T(1));
     const uint32_t ia = (uint32_t)((p * N + yi) * la.la.pitch + kz);
 #pragma unroll
     for (int c = 0; c < 3; ++c) q[c][i] = scale(ld_masked(la.A + c * la.la.cs, ia, ok), fa);
     if (la.B != nullptr) {
-      const float fb = la.cB * (la.eB ? la.eB[k2] : 1.f);
+      const T fb = la.cB * (la.eB ? la.eB[k2] : T(1));
       const uint32_t ib = (uint32_t)((p * N + yi) * la.lb.pitch + kz);
 #pragma unroll
       for (int c = 0; c < 3; ++c) q[c][i] = q[c][i] + scale(ld_masked(la.B + c * la.lb.cs, ib, ok), fb);
     }
     if (k2 == 0) {
-      q[0][i] = q[1][i] = q[2][i] = cx(0.f, 0.f);
+      q[0][i] = q[1][i] = q[2][i] = cx(T(0), T(0));
     } else {
-      const float rk2 = 1.f / float(k2);
-      const float kxr = float(kx), kyr = float(ky), kzr = float(kz);
-      const Cx<float> kd = scale(scale(q[0][i], kxr) + scale(q[1][i], kyr) + scale(q[2][i], kzr), rk2);
+      const T rk2 = T(1) / T(k2);
+      const T kxr = T(kx), kyr = T(ky), kzr = T(kz);
+      const Cx<T> kd = scale(scale(q[0][i], kxr) + scale(q[1][i], kyr) + scale(q[2][i], kzr), rk2);
       q[0][i] = q[0][i] - scale(kd, kxr);
       q[1][i] = q[1][i] - scale(kd, kyr);
       q[2][i] = q[2][i] - scale(kd, kzr);
     }
     if (sh.on) {
-      const Cx<float> phi = cmul(phx[p], phyz);
+      const Cx<T> phi = cmul(phx[p], phyz);
 #pragma unroll
       for (int c = 0; c < 3; ++c) q[c][i] = cmul(q[c][i], phi);
     }
@@ -96,32 +97,33 @@ f_xlam(LamArgs<float> la, Cx<float>* __restrict__ W, const Cx<float>* __restrict
 // split by the line's own threads into fields 0..5 = g1x, g1y, g1z, g2x, g2y, g2z.
 template <typename C, int P>
 __global__ void __launch_bounds__(P * C::TPL)
-f_zadj(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Geom g) {
+f_zadj(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ twg, Geom g) {
+  using T = typename C::T;
   constexpr int N = C::N, TPL = C::TPL, EPT = C::EPT, HN = N / 2, NT = P * TPL;
   using FI = RegFft<N, TPL, +1, typename C::Inv>;
   using FF = RegFft<N, TPL, -1, typename C::Fwd>;
   static_assert(FI::RL == FF::R0, "the forward transform must start with the last inverse radix");
   constexpr bool WV = (64 % TPL == 0);  // else a line straddles wavefronts: block barriers
   constexpr int LP = line_pitch(N);
-  __shared__ Cx<float> tw[N];
-  __shared__ Cx<float> xb[P * LP];  // exchanges
-  __shared__ Cx<float> sp[P * N];   // one forward spectrum per line
+  __shared__ Cx<T> tw[N];
+  __shared__ Cx<T> xb[P * LP];  // exchanges
+  __shared__ Cx<T> sp[P * N];   // one forward spectrum per line
   const int tid = threadIdx.x;
   const int p = tid / TPL, t = tid % TPL;
   const uint32_t line = (uint32_t)blockIdx.x * P + p;
   for (int i = tid; i < N; i += NT) tw[i] = twg[i];
   __syncthreads();  // the transforms below synchronise only within a wavefront
-  const LineView<float, 1> lv{xb + p * LP};
+  const LineView<T, 1> lv{xb + p * LP};
   const uint32_t lbase = line * (uint32_t)g.kzp;
-  Cx<float> z[4][EPT], v[EPT];
+  Cx<T> z[4][EPT], v[EPT];
 #pragma unroll
   for (int q = 0; q < 5; ++q) {
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
       const int pos = FI::in_at(t, i);
       const int k = pos <= HN ? pos : N - pos;
-      const Cx<float> a = ld_masked(W + (2 * q) * g.wcomp, lbase + k, k < g.kzn);
-      const Cx<float> bb = q < 4 ? ld_masked(W + (2 * q + 1) * g.wcomp, lbase + k, k < g.kzn) : cx(0.f, 0.f);
+      const Cx<T> a = ld_masked(W + (2 * q) * g.wcomp, lbase + k, k < g.kzn);
+      const Cx<T> bb = q < 4 ? ld_masked(W + (2 * q + 1) * g.wcomp, lbase + k, k < g.kzn) : cx(T(0), T(0));
       if (pos == 0 || pos == HN) v[i] = cx(a.re, bb.re);
       else if (pos < HN) v[i] = cx(a.re - bb.im, a.im + bb.re);
       else v[i] = cx(a.re + bb.im, bb.re - a.im);
@@ -132,11 +134,11 @@ f_zadj(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Geom g) {
       for (int i = 0; i < EPT; ++i) z[q][i] = v[i];
     }
   }
-  float g1[3][EPT], g2[3][EPT];
+  T g1[3][EPT], g2[3][EPT];
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
-    const float ux = z[0][i].re, uy = z[0][i].im, uz = z[1][i].re, wx = z[1][i].im;
-    const float wy = z[2][i].re, wz = z[2][i].im, lx = z[3][i].re, ly = z[3][i].im, lz = v[i].re;
+    const T ux = z[0][i].re, uy = z[0][i].im, uz = z[1][i].re, wx = z[1][i].im;
+    const T wy = z[2][i].re, wz = z[2][i].im, lx = z[3][i].re, ly = z[3][i].im, lz = v[i].re;
     g1[0][i] = wy * lz - wz * ly;
     g1[1][i] = wz * lx - wx * lz;
     g1[2][i] = wx * ly - wy * lx;
@@ -148,8 +150,8 @@ f_zadj(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Geom g) {
   for (int q = 0; q < 3; ++q) {
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
-      const float re = q == 0 ? g1[0][i] : (q == 1 ? g1[2][i] : g2[1][i]);
-      const float im = q == 0 ? g1[1][i] : (q == 1 ? g2[0][i] : g2[2][i]);
+      const T re = q == 0 ? g1[0][i] : (q == 1 ? g1[2][i] : g2[1][i]);
+      const T im = q == 0 ? g1[1][i] : (q == 1 ? g2[0][i] : g2[2][i]);
       v[i] = cx(re, im);
     }
     FF::template run<WV>(v, t, lv, tw);
@@ -159,10 +161,10 @@ f_zadj(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Geom g) {
       if (FF::out_ok(t, i)) sp[p * N + FF::out_pos(t, i)] = v[i];
     exchange_barrier<WV>();
     for (int k = t; k < g.kzn; k += TPL) {
-      const Cx<float> c1 = sp[p * N + k], c2 = sp[p * N + ((N - k) % N)];
+      const Cx<T> c1 = sp[p * N + k], c2 = sp[p * N + ((N - k) % N)];
       const uint32_t off = lbase + k;
-      st_off(W + (2 * q) * g.wcomp, off, cx(0.5f * (c1.re + c2.re), 0.5f * (c1.im - c2.im)));
-      st_off(W + (2 * q + 1) * g.wcomp, off, cx(0.5f * (c1.im + c2.im), -0.5f * (c1.re - c2.re)));
+      st_off(W + (2 * q) * g.wcomp, off, cx(T(0.5) * (c1.re + c2.re), T(0.5) * (c1.im - c2.im)));
+      st_off(W + (2 * q + 1) * g.wcomp, off, cx(T(0.5) * (c1.im + c2.im), T(-0.5) * (c1.re - c2.re)));
     }
   }
 }
@@ -170,23 +172,25 @@ f_zadj(Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Geom g) {
 // ------------------------------------------------------------------ forward x pass
 // V = M conj(phi) (g1 + i k x g2) / N^3 from fields 0..5, then the adjoint stage
 // combination AOP (tiles as f_xfwd; full mode covers every tile and writes zeros
-// outside the retained set).
+// outside the retained set).  AOP_ANY: the combination comes from the arguments.
 template <typename C, int AOP>
-__global__ void __launch_bounds__(kFastL * C::TPL)
-f_xadj(const Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Shift sh,
-       const int2* __restrict__ tiles, Geom g, AdjArgs<float> a) {
+__global__ void __launch_bounds__(C::L * C::TPL)
+f_xadj(const Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ twg, Shift sh,
+       const int2* __restrict__ tiles, Geom g, AdjArgs<typename C::T> a) {
+  using T = typename C::T;
   constexpr int N = C::N, TPL = C::TPL, EPT = C::EPT;
   using F = RegFft<N, TPL, -1, typename C::Fwd>;
-  __shared__ Cx<float> tw[N];
-  __shared__ Cx<float> phx[N];
-  __shared__ Cx<float> phc[kFastL];
-  __shared__ Cx<float> xb[N * kFastLp];
+  __shared__ Cx<T> tw[N];
+  __shared__ Cx<T> phx[N];
+  __shared__ Cx<T> phc[C::L];
+  __shared__ Cx<T> xb[N * C::LP];
+  const int aop = AOP == AOP_ANY ? a.op : AOP;
   const int tid = threadIdx.x;
-  const int l = tid % kFastL, t = tid / kFastL;
+  const int l = tid % C::L, t = tid / C::L;
   int yi, kz0;
   if (a.full) {
     yi = blockIdx.x / a.ntzf;
-    kz0 = (blockIdx.x % a.ntzf) * kFastL;
+    kz0 = (blockIdx.x % a.ntzf) * C::L;
   } else {
     const int2 tile = tiles[blockIdx.x];
     yi = tile.x;
@@ -195,21 +199,21 @@ f_xadj(const Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Shift
   const int kz = kz0 + l;
   const int ky = kval(yi, N);
   const bool active = line_active(g, ky, kz0);
-  const LineView<float, kFastLp> lv{xb + l};
-  Cx<float> r[3][EPT], v[EPT];
-  Cx<float> phyz = cx(1.f, 0.f);
+  const LineView<T, C::LP> lv{xb + l};
+  Cx<T> r[3][EPT], v[EPT];
+  Cx<T> phyz = cx(T(1), T(0));
   if (active) {
-    for (int i = tid; i < N; i += kFastL * TPL) tw[i] = twg[i];
+    for (int i = tid; i < N; i += C::L * TPL) tw[i] = twg[i];
     if (sh.on) {
-      phase_row(phx, N, sh.s[0], tid, kFastL * TPL);
+      phase_row(phx, N, sh.s[0], tid, C::L * TPL);
       phase_cols(phc, ky, kz0, sh, N, tid);
     }
     const bool col = kz < g.kzn;
     const uint32_t wbase = (uint32_t)(yi * g.kzp + kz0) + l, wstep = (uint32_t)(N * g.kzp);
-    const float kyf = float(ky), kzf = float(kz);
+    const T kyf = T(ky), kzf = T(kz);
 #pragma unroll
     for (int f = 0; f < 6; ++f) {
-      Cx<float>* dst = f < 3 ? r[f] : v;
+      Cx<T>* dst = f < 3 ? r[f] : v;
 #pragma unroll
       for (int i = 0; i < EPT; ++i)
         dst[i] = ld_masked(W + f * g.wcomp, (uint32_t)F::in_at(t, i) * wstep + wbase, col && F::in_ok(t, i));
@@ -217,8 +221,8 @@ f_xadj(const Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Shift
       if (f >= 3) {
 #pragma unroll
         for (int i = 0; i < EPT; ++i) {
-          const float kxf = float(kval(F::out_at(t, i), N));
-          const Cx<float> iv = mul_i(v[i]);
+          const T kxf = T(kval(F::out_at(t, i), N));
+          const Cx<T> iv = mul_i(v[i]);
           if (f == 3) {         // i k x (g2x, 0, 0) = (0, i kz g2x, -i ky g2x)
             r[1][i] = r[1][i] + scale(iv, kzf);
             r[2][i] = r[2][i] - scale(iv, kyf);
@@ -237,7 +241,7 @@ f_xadj(const Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Shift
   if (kz >= g.h || (!a.full && kz >= g.kzn)) return;
   const LineTest keep = line_test(g, ky, kz);
   const bool line_kept = active && kz < g.kzn;
-  const float inv_n3 = 1.f / (float(N) * float(N) * float(N));
+  const T inv_n3 = T(1) / (T(N) * T(N) * T(N));
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
     if (!F::out_ok(t, i)) continue;  // no point in this register
@@ -246,27 +250,27 @@ f_xadj(const Cx<float>* __restrict__ W, const Cx<float>* __restrict__ twg, Shift
     const uint32_t io0 = (uint32_t)((p * N + yi) * a.lo0.pitch + kz);
     if (!(line_kept && keep(kx))) {
       if (a.full)
-        for (int c = 0; c < 3; ++c) st_off(a.out0 + c * a.lo0.cs, io0, cx(0.f, 0.f));
+        for (int c = 0; c < 3; ++c) st_off(a.out0 + c * a.lo0.cs, io0, cx(T(0), T(0)));
       continue;
     }
-    Cx<float> V[3] = {scale(r[0][i], inv_n3), scale(r[1][i], inv_n3), scale(r[2][i], inv_n3)};
+    Cx<T> V[3] = {scale(r[0][i], inv_n3), scale(r[1][i], inv_n3), scale(r[2][i], inv_n3)};
     if (sh.on) {
-      const Cx<float> phi = cmul(phx[p], phyz);
+      const Cx<T> phi = cmul(phx[p], phyz);
 #pragma unroll
       for (int c = 0; c < 3; ++c) V[c] = cmulc(V[c], phi);
     }
     const int k2 = kx * kx + ky * ky + kz * kz;
-    const float eh = a.eh[k2], edt = a.edt[k2];
+    const T eh = a.eh[k2], edt = a.edt[k2];
     const uint32_t ii0 = (uint32_t)((p * N + yi) * a.li0.pitch + kz);
     const uint32_t ii1 = (uint32_t)((p * N + yi) * a.li1.pitch + kz);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      Cx<float>* out0 = a.out0 + c * a.lo0.cs;
-      if (AOP == AOP_STORE) {
+      Cx<T>* out0 = a.out0 + c * a.lo0.cs;
+      if (aop == AOP_STORE) {
         st_off(out0, io0, V[c]);
-      } else if (AOP == AOP_ACC) {
+      } else if (aop == AOP_ACC) {
         st_off(out0, io0, a.in1[c * a.li1.cs + ii1] + V[c]);
-      } else if (AOP == AOP_HEUN) {
+      } else if (aop == AOP_HEUN) {
         st_off(out0, io0, scale(a.in0[c * a.li0.cs + ii0] + a.in1[c * a.li1.cs + ii1], edt) + V[c]);
       } else {  // AOP_EXACT
         st_off(out0, io0, scale(a.in0[c * a.li0.cs + ii0], edt) + scale(a.in1[c * a.li1.cs + ii1], eh) + V[c]);

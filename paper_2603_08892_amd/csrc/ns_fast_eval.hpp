@@ -1,6 +1,7 @@
-// ns_fast_eval.hpp -- launch sequences of the specialised FP32 passes of one
-// grid size; included by that size's translation unit (fast_<N>.hip), which
-// instantiates them for every epilogue and adjoint op with NS_FAST_INSTANTIATE.
+// ns_fast_eval.hpp -- launch sequences of the specialised passes of one grid size;
+// included by that size's translation unit: fast_<N>.hip instantiates them for every
+// epilogue and adjoint op with NS_FAST_INSTANTIATE, size_passes.hip (ns_size_eval.hpp)
+// with the ops as arguments.
 #pragma once
 
 #include "ns_host_impl.hpp"
@@ -22,29 +23,30 @@ template <> struct FastOf<240> { using type = ns::Fast240; };
 template <> struct FastOf<270> { using type = ns::Fast270; };
 template <> struct FastOf<360> { using type = ns::Fast360; };
 
-// Specialised FP32 passes for one compile-time size (same semantics and layout).
+// Specialised passes for one compile-time size (same semantics and layout).
 template <typename C, int OP, int FEED>
-ns_status eval_fast(ns_ctx* c, const Cx<float>* in, ns::Lay lin, const ns::Shift& sh, const EpiArgs<float>& a,
-                    bool front, const ns::Shift& sh2) {
+ns_status eval_fast(ns_ctx* c, const Cx<typename C::T>* in, ns::Lay lin, const ns::Shift& sh,
+                    const EpiArgs<typename C::T>& a, bool front, const ns::Shift& sh2) {
+  using T = typename C::T;
   const Layout& l = c->lay;
   const Geom& g = l.g;
-  Ptrs<float> p = ptrs<float>(c);
+  Ptrs<T> p = ptrs<T>(c);
   constexpr int N = C::N, P = C::PZ;
   hipError_t e;
   const int ntiles = l.ntiles_active;
   if (ntiles > 0) {
     if (front) {
       if ((e = tstart(c, 0)) != hipSuccess) return hip_check(c, e, "timing event");
-      hipLaunchKernelGGL((ns::f_xinv<typename C::XInv, !C::YC>), dim3(ntiles), dim3(ns::kFastL * C::XInv::TPL), 0,
+      hipLaunchKernelGGL((ns::f_xinv<typename C::XInv, !C::YC>), dim3(ntiles), dim3(C::XInv::L * C::XInv::TPL), 0,
                          c->stream, in, lin, p.W, p.tw, sh, p.tiles, g);
       if ((e = tstop(c)) != hipSuccess) return hip_check(c, e, "timing event");
     }
     if ((e = tstart(c, 1)) != hipSuccess) return hip_check(c, e, "timing event");
     if constexpr (C::YC)
-      hipLaunchKernelGGL(ns::f_ycurl<typename C::Y>, dim3(2 * N * l.ntz), dim3(ns::kFastL * C::Y::TPL), 0,
+      hipLaunchKernelGGL(ns::f_ycurl<typename C::Y>, dim3(2 * N * l.ntz), dim3(C::Y::L * C::Y::TPL), 0,
                          c->stream, p.W, p.tw, l.ntz, g);
     else
-      hipLaunchKernelGGL((ns::f_ypass<typename C::Y, +1>), dim3(6 * N * l.ntz), dim3(ns::kFastL * C::Y::TPL), 0,
+      hipLaunchKernelGGL((ns::f_ypass<typename C::Y, +1>), dim3(6 * N * l.ntz), dim3(C::Y::L * C::Y::TPL), 0,
                          c->stream, p.W, p.tw, l.ntz, g);
     if ((e = tstop(c)) != hipSuccess) return hip_check(c, e, "timing event");
     if ((e = tstart(c, 2)) != hipSuccess) return hip_check(c, e, "timing event");
@@ -52,7 +54,7 @@ ns_status eval_fast(ns_ctx* c, const Cx<float>* in, ns::Lay lin, const ns::Shift
                        p.W, p.tw, g);
     if ((e = tstop(c)) != hipSuccess) return hip_check(c, e, "timing event");
     if ((e = tstart(c, 3)) != hipSuccess) return hip_check(c, e, "timing event");
-    hipLaunchKernelGGL((ns::f_ypass<typename C::Y, -1>), dim3(3 * N * l.ntz), dim3(ns::kFastL * C::Y::TPL), 0,
+    hipLaunchKernelGGL((ns::f_ypass<typename C::Y, -1>), dim3(3 * N * l.ntz), dim3(C::Y::L * C::Y::TPL), 0,
                        c->stream, p.W, p.tw, l.ntz, g);
     if ((e = tstop(c)) != hipSuccess) return hip_check(c, e, "timing event");
   }
@@ -60,7 +62,7 @@ ns_status eval_fast(ns_ctx* c, const Cx<float>* in, ns::Lay lin, const ns::Shift
   if ((e = tstart(c, FEED ? 5 : 4)) != hipSuccess) return hip_check(c, e, "timing event");
   if (nblk > 0)
     hipLaunchKernelGGL((ns::f_xfwd<typename C::XFwd, OP, FEED, !C::YC>), dim3(nblk),
-                       dim3(ns::kFastL * C::XFwd::TPL), 0, c->stream, p.W, p.tw, sh, sh2, p.tiles, g, a);
+                       dim3(C::XFwd::L * C::XFwd::TPL), 0, c->stream, p.W, p.tw, sh, sh2, p.tiles, g, a);
   if ((e = tstop(c)) != hipSuccess) return hip_check(c, e, "timing event");
   return hip_check(c, hipGetLastError(), "nonlinear-term launch");
 }
@@ -86,31 +88,32 @@ ns_status eval_fast_chain(ns_ctx* c, const Cx<float>* in, ns::Lay lin, const ns:
   return eval_fast<C, OP, 0>(c, in, lin, sh, a, front, sh);
 }
 
-// Specialised FP32 passes of one transposed evaluation (same semantics and layout).
+// Specialised passes of one transposed evaluation (same semantics and layout).
 template <typename C, int AOP>
-ns_status adj_eval_fast(ns_ctx* c, const Cx<float>* st, ns::Lay lst, const ns::Shift& sh,
-                        const LamArgs<float>& la, AdjArgs<float> aa) {
+ns_status adj_eval_fast(ns_ctx* c, const Cx<typename C::T>* st, ns::Lay lst, const ns::Shift& sh,
+                        const LamArgs<typename C::T>& la, AdjArgs<typename C::T> aa) {
+  using T = typename C::T;
   const Layout& l = c->lay;
   const Geom& g = l.g;
-  Ptrs<float> p = ptrs<float>(c);
+  Ptrs<T> p = ptrs<T>(c);
   constexpr int N = C::N, P = C::PZA;
   const int ntiles = l.ntiles_active;
   if (ntiles > 0) {
-    hipLaunchKernelGGL((ns::f_xinv<typename C::XInv, true>), dim3(ntiles), dim3(ns::kFastL * C::XInv::TPL), 0,
+    hipLaunchKernelGGL((ns::f_xinv<typename C::XInv, true>), dim3(ntiles), dim3(C::XInv::L * C::XInv::TPL), 0,
                        c->stream, st, lst, p.W, p.tw, sh, p.tiles, g);
-    hipLaunchKernelGGL(ns::f_xlam<typename C::XInv>, dim3(ntiles), dim3(ns::kFastL * C::XInv::TPL), 0,
+    hipLaunchKernelGGL(ns::f_xlam<typename C::XInv>, dim3(ntiles), dim3(C::XInv::L * C::XInv::TPL), 0,
                        c->stream, la, p.W, p.tw, sh, p.tiles, g);
-    hipLaunchKernelGGL((ns::f_ypass<typename C::Y, +1>), dim3(9 * N * l.ntz), dim3(ns::kFastL * C::Y::TPL), 0,
+    hipLaunchKernelGGL((ns::f_ypass<typename C::Y, +1>), dim3(9 * N * l.ntz), dim3(C::Y::L * C::Y::TPL), 0,
                        c->stream, p.W, p.tw, l.ntz, g);
     hipLaunchKernelGGL((ns::f_zadj<typename C::ZAdj, P>), dim3(N * N / P), dim3(P * C::ZAdj::TPL), 0, c->stream,
                        p.W, p.tw, g);
-    hipLaunchKernelGGL((ns::f_ypass<typename C::Y, -1>), dim3(6 * N * l.ntz), dim3(ns::kFastL * C::Y::TPL), 0,
+    hipLaunchKernelGGL((ns::f_ypass<typename C::Y, -1>), dim3(6 * N * l.ntz), dim3(C::Y::L * C::Y::TPL), 0,
                        c->stream, p.W, p.tw, l.ntz, g);
   }
   aa.ntzf = l.ntzf;
   const int nblk = aa.full ? N * l.ntzf : ntiles;
   if (nblk > 0)
-    hipLaunchKernelGGL((ns::f_xadj<typename C::XFwd, AOP>), dim3(nblk), dim3(ns::kFastL * C::XFwd::TPL), 0,
+    hipLaunchKernelGGL((ns::f_xadj<typename C::XFwd, AOP>), dim3(nblk), dim3(C::XFwd::L * C::XFwd::TPL), 0,
                        c->stream, p.W, p.tw, sh, p.tiles, g, aa);
   return hip_check(c, hipGetLastError(), "adjoint launch");
 }

@@ -9,6 +9,7 @@
 #include <mutex>
 
 #include "ns_host_impl.hpp"
+#include "ns_size_plans.hpp"
 #include "ns_aux_kernels.hpp"
 #include "ns_model1d.hpp"
 
@@ -98,13 +99,28 @@ const char* validate(const ns_config* c) {
   return nullptr;
 }
 
-// Sizes with specialised FP32 passes (ns_fast.hpp), unless the config asks for the
-// size-generic ones.
+// The passes of size n with the stage as an argument (ns_size_plans.hpp), null where
+// the size has none.
+template <typename R>
+const SizePasses<R>* sized_passes(int n) {
+#define NS_SIZE_CASE(T, N) \
+  if constexpr (std::is_same<R, T>::value) { if (n == N) return size_passes<R, N>(); }
+  NS_FOR_EACH_SIZE(NS_SIZE_CASE)
+#undef NS_SIZE_CASE
+  return nullptr;
+}
+
+// Sizes with FP32 passes specialised per stage (ns_fast.hpp).
+bool stage_size(int n) {
+  return n == 64 || n == 128 || n == 144 || n == 160 || n == 192 || n == 216 || n == 240 || n == 256 || n == 270 ||
+         n == 324 || n == 360 || n == 384 || n == 512;
+}
+
+// Whether the config runs specialised passes (unless it asks for the size-generic ones).
 bool fast_size(const ns_config* c) {
-  const int n = c->n;
-  return c->precision == NS_FP32 && !(c->flags & NS_CFG_GENERIC_PASSES) &&
-         (n == 64 || n == 128 || n == 144 || n == 160 || n == 192 || n == 216 || n == 240 || n == 256 ||
-          n == 270 || n == 324 || n == 360 || n == 384 || n == 512);
+  if (c->flags & NS_CFG_GENERIC_PASSES) return false;
+  if (c->precision == NS_FP64) return sized_passes<double>(c->n) != nullptr;
+  return stage_size(c->n) || sized_passes<float>(c->n) != nullptr;
 }
 
 bool make_layout(const ns_config* c, Layout* lay) {
@@ -132,7 +148,7 @@ bool make_layout(const ns_config* c, Layout* lay) {
   for (;;) {
     tx = (n * L + kEpt - 1) / kEpt;
     tx = (tx + 63) / 64 * 64;
-    // the specialised passes always tile 16 columns (the generic kernels, which
+    // the specialised passes always tile a 128-byte row (the generic kernels, which
     // would need more than 512 threads for that at N > 256, are not used then)
     if (tx <= 512 || L == 1 || fast_size(c)) break;
     L /= 2;
@@ -203,6 +219,13 @@ bool make_layout(const ns_config* c, Layout* lay) {
   return true;
 }
 
+// The context's passes with the stage as an argument, if it runs them.
+template <typename R>
+const SizePasses<R>* sized(const ns_ctx* c) {
+  if constexpr (std::is_same<R, float>::value) return c->sized32;
+  else return c->sized64;
+}
+
 // One evaluation of the nonlinear term on `in` (layout lin) with the shift s (NULL
 // or all zero = unshifted); the x-forward epilogue applies OP with the operands
 // and layouts in a.
@@ -231,6 +254,7 @@ ns_status eval(ns_ctx* c, const Cx<R>* in, ns::Lay lin, const double* s, EpiArgs
       default: break;
     }
   }
+  if (const SizePasses<R>* z = sized<R>(c)) return z->eval(c, OP, in, lin, sh, a, ch);
   if (ch) ch->fused = false;  // the size-generic passes run every x-inverse pass on its own
   const size_t lds = lds_strided(l);
   const int ntiles = l.ntiles_active;
@@ -584,6 +608,7 @@ ns_status adj_eval(ns_ctx* c, const Cx<R>* st, ns::Lay lst, const double* s, con
       default: break;
     }
   }
+  if (const SizePasses<R>* z = sized<R>(c)) return z->adj(c, AOP, st, lst, sh, la, aa);
   const size_t lds = lds_strided(l);
   const int ntiles = l.ntiles_active;
   if (ntiles > 0) {
@@ -840,7 +865,11 @@ ns_status ns_init(const ns_config* cfg, void* workspace, size_t ws_bytes, ns_ctx
     return fail(nullptr, NS_ERR_SIZE, msg);
   }
   c->ws = static_cast<char*>(workspace);
-  if (fast_size(cfg) && c->lay.g.L == ns::kFastL) c->fast = cfg->n;
+  if (fast_size(cfg)) {
+    if (cfg->precision == NS_FP64) c->sized64 = sized_passes<double>(cfg->n);
+    else if (stage_size(cfg->n)) c->fast = cfg->n;
+    else c->sized32 = sized_passes<float>(cfg->n);
+  }
   // twiddles W_N^t = exp(-2 pi i t/N), long double, rounded once
   const int n = cfg->n;
   const long double pi = 3.141592653589793238462643383279502884L;

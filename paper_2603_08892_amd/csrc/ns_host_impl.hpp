@@ -57,6 +57,28 @@ struct Layout {
   size_t total;
 };
 
+// Chaining of consecutive evaluations.  In: front_done = this evaluation's
+// x-inverse pass already ran (fused into the previous x-forward pass); feed = the
+// stage output that is the next evaluation's input (0 none, 1 out0, 2 out1) and
+// next_s its shift.  Out: fused = the next evaluation's x-inverse pass ran here
+// (only the specialised passes fuse, and only into a stage that is not in full
+// mode); an out1 that feeds is then not stored.
+struct Chain {
+  bool front_done = false;
+  int feed = 0;
+  const double* next_s = nullptr;
+  bool fused = false;
+};
+
+// The passes of one grid size and type with the stage operation as an argument:
+// one evaluation of the nonlinear term and one transposed evaluation.
+template <typename R>
+struct SizePasses {
+  ns_status (*eval)(ns_ctx* c, int op, const Cx<R>* in, ns::Lay lin, const ns::Shift& sh, EpiArgs<R> a, Chain* ch);
+  ns_status (*adj)(ns_ctx* c, int aop, const Cx<R>* st, ns::Lay lst, const ns::Shift& sh, const LamArgs<R>& la,
+                   AdjArgs<R> aa);
+};
+
 }  // namespace nsh
 
 struct ns_ctx {
@@ -68,7 +90,9 @@ struct ns_ctx {
   double* pin_spec = nullptr;    // pinned host copy of the last spectra reduction
   hipEvent_t spec_ev = nullptr;  // recorded after that copy
   bool spec_pending = false;     // a reduction was enqueued and not yet waited for
-  int fast = 0;       // N of the specialised FP32 passes in use (0: generic passes)
+  int fast = 0;       // N of the per-stage specialised FP32 passes in use (0: none)
+  const nsh::SizePasses<float>* sized32 = nullptr;   // the passes of one size with the stage as an
+  const nsh::SizePasses<double>* sized64 = nullptr;  // argument, if it has them (else generic passes)
   double etab_dt = -1.0;  // dt of the integrating-factor tables now in the workspace
   // per-pass timing: events[2 i], events[2 i + 1] bracket launch i of pass tpass[i]
   bool budget = false;     // update the energy budget after every step
@@ -195,19 +219,6 @@ inline hipError_t launch_xfwd(ns_ctx* c, const Ptrs<R>& p, const ns::Shift& sh, 
   return hipGetLastError();
 }
 
-// Chaining of consecutive evaluations.  In: front_done = this evaluation's
-// x-inverse pass already ran (fused into the previous x-forward pass); feed = the
-// stage output that is the next evaluation's input (0 none, 1 out0, 2 out1) and
-// next_s its shift.  Out: fused = the next evaluation's x-inverse pass ran here
-// (only the specialised passes fuse, and only into a stage that is not in full
-// mode); an out1 that feeds is then not stored.
-struct Chain {
-  bool front_done = false;
-  int feed = 0;
-  const double* next_s = nullptr;
-  bool fused = false;
-};
-
 // Specialised FP32 passes of size N (defined and instantiated for every op in the
 // translation unit of that size): one evaluation of the nonlinear term, and one
 // transposed evaluation.
@@ -217,5 +228,10 @@ ns_status fast_eval(ns_ctx* c, const Cx<float>* in, ns::Lay lin, const ns::Shift
 template <int N, int AOP>
 ns_status fast_adj_eval(ns_ctx* c, const Cx<float>* st, ns::Lay lst, const ns::Shift& sh,
                         const LamArgs<float>& la, AdjArgs<float> aa);
+
+// The passes with the stage as an argument of the sizes in ns_size_plans.hpp, defined
+// in the translation unit of each size and type.
+template <typename R, int N>
+const SizePasses<R>* size_passes();
 
 }  // namespace nsh

@@ -334,8 +334,10 @@ enum EpiOp {
   OP_MID1 = 11,  // out0 = E_h (S0 + dt/2 N)
   OP_MID2 = 12,  // out0 = E_dt S0 + dt E_h N
   OP_EUL = 13,   // out0 = E_dt (S0 + dt N)
-  OP_EULAV = 14  // out0 = E_dt (S0 + dt w (in1 + N))
+  OP_EULAV = 14, // out0 = E_dt (S0 + dt w (in1 + N))
+  OP_ANY = -1    // kernels only: the operation is an argument (EpiArgs::op)
 };
+constexpr int FEED_ANY = 3;  // kernels only: the fed output is an argument (EpiArgs::feed)
 // w (EpiArgs::w) weighs each of the shifted evaluations summed in in1 + N: 1/2 for
 // the two-shift average, 1/8 for the average over the eight shifts in {0, 1/2}^3.
 
@@ -349,6 +351,19 @@ __host__ __device__ constexpr bool op_forced(int op) {
 // Ops whose stage formula uses the integrating factors E_h and E_dt.
 __host__ __device__ constexpr bool op_uses_etab(int op) {
   return op != OP_STORE && op != OP_AVG && op != OP_ACC;
+}
+
+// Ops that read S0 (in0), that read the accumulator (in1) and that have a second output.
+__host__ __device__ constexpr bool op_reads0(int op) {
+  return op == OP_HEUN1 || op == OP_EX1B || op == OP_EX2B || op == OP_RK4_0 || op == OP_RK4_1 || op == OP_RK4_2 ||
+         op == OP_MID1 || op == OP_MID2 || op == OP_EUL || op == OP_EULAV;
+}
+__host__ __device__ constexpr bool op_reads1(int op) {
+  return op == OP_AVG || op == OP_HEUN2 || op == OP_EX1B || op == OP_EX2B || op == OP_RK4_1 || op == OP_RK4_2 ||
+         op == OP_RK4_3 || op == OP_ACC || op == OP_EULAV;
+}
+__host__ __device__ constexpr bool op_writes1(int op) {
+  return op == OP_HEUN1 || op == OP_RK4_0 || op == OP_RK4_1 || op == OP_RK4_2;
 }
 
 // Stage outputs that are the next evaluation's input in the step sequences (feed
@@ -373,6 +388,7 @@ struct EpiArgs {
   R w;                // weight of each summed evaluation (OP_EX1B, OP_EX2B, OP_EULAV)
   int full;           // 1: blocks cover every (k_y, k_z tile) of the half spectrum and write zeros outside
   int ntzf;           // k_z tiles over [0, N/2] in full mode
+  int op, feed;       // the EpiOp and the fed output (1: out0, 2: out1) of the OP_ANY kernels
 };
 
 template <typename R, int EPT, int OP>

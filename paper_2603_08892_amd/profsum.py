@@ -104,7 +104,7 @@ def source_hash():
 
 def classify(name):
     """(grid size or None, pass name) of a kernel name as rocprofv3 prints it."""
-    m = re.match(r"(?:void )?ns::(\w+)<ns::LinePlan<(\d+),", name)
+    m = re.match(r"(?:void )?ns::(\w+)<ns::LinePlanD?<(\d+),", name)
     if m:
         kern, n = m.group(1), int(m.group(2))
         if kern == "f_xinv":
