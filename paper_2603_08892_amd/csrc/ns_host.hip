@@ -992,14 +992,8 @@ ns_status check1d(int32_t n, double ct, int32_t batch, const void* a, const void
 
 ns_status launch1d(const ns1d::Args& a, int32_t batch, void* stream) {
   if (batch == 0) return NS_OK;
-  const size_t lds = ns1d::lds_bytes(a.n);
-  hipError_t e = allow_lds(ns1d::k_model1d, lds);
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(ns1d::k_model1d, dim3((unsigned)batch), dim3(ns1d::kThreads), lds,
-                       static_cast<hipStream_t>(stream), a);
-    e = hipGetLastError();
-  }
-  return hip_check(nullptr, e, "1D model launch");
+  ns1d::launch(a, batch, static_cast<hipStream_t>(stream));
+  return hip_check(nullptr, hipGetLastError(), "1D model launch");
 }
 
 }  // namespace
@@ -1010,8 +1004,14 @@ ns_status ns1d_nonlinear(const void* s_hat, void* n_hat, int32_t n, double ct, i
   ns_status st = check1d(n, ct, batch, s_hat, n_hat, &kmax);
   if (st != NS_OK) return st;
   if (!std::isfinite(shift)) return fail(nullptr, NS_ERR_ARG, "shift must be finite");
-  ns1d::Args a{static_cast<const double2*>(s_hat), static_cast<double2*>(n_hat), n, n / 2 + 1, kmax, 0.0, 0, -1,
-               shift};
+  ns1d::Args a{};
+  a.in = static_cast<const double2*>(s_hat);
+  a.out = static_cast<double2*>(n_hat);
+  a.n = n;
+  a.h = n / 2 + 1;
+  a.kmax = kmax;
+  a.shift = shift;
+  ns1d::make_scheme(&a, -1, 0.0);
   return launch1d(a, batch, stream);
 }
 
@@ -1024,8 +1024,13 @@ ns_status ns1d_step(void* s_hat, int32_t n, double ct, int32_t batch, double dt,
   if (nsteps < 0) return fail(nullptr, NS_ERR_ARG, "nsteps must be >= 0");
   if (scheme < NS1D_EULER || scheme > NS1D_RK4) return fail(nullptr, NS_ERR_ARG, "unknown 1D scheme");
   if (nsteps == 0) return NS_OK;
-  ns1d::Args a{static_cast<const double2*>(s_hat), static_cast<double2*>(s_hat), n, n / 2 + 1, kmax, dt, nsteps,
-               scheme, 0.0};
+  ns1d::Args a{};
+  a.in = a.out = static_cast<double2*>(s_hat);
+  a.n = n;
+  a.h = n / 2 + 1;
+  a.kmax = kmax;
+  a.nsteps = nsteps;
+  ns1d::make_scheme(&a, scheme, dt);
   return launch1d(a, batch, stream);
 }
 
