@@ -6,108 +6,208 @@
 
 namespace ns {
 
-// Shell of an integer |k|^2: smallest n with n(n+1) >= k^2, i.e. n(n-1) < k^2 <= n(n+1).
-__device__ __forceinline__ int shell_of(long long k2) {
-  const int r = isqrt_ll(k2);
-  return ((long long)r * (r + 1) >= k2) ? r : r + 1;
+// LDS bins of one wavefront of k_spectra: E, D(, T) by shell, E by |k_x| and by |k_y|, the
+// lanes' E by k_z, E at k_z = N/2, and the five totals.
+__host__ __device__ constexpr int spectra_wave_bins(int n, int nsh, bool nh) {
+  return (nh ? 3 : 2) * nsh + 2 * (n / 2 + 1) + 64 + 6;
+}
+
+// Shell of an integer |k|^2 < 2^24 (exact in FP32): smallest n with n(n+1) >= k^2, i.e.
+// n(n-1) < k^2 <= n(n+1).
+__device__ __forceinline__ int shell_small(int k2) {
+  int r = (int)sqrtf((float)k2);
+  r -= r * r > k2;
+  r += (r + 1) * (r + 1) <= k2;
+  return r * (r + 1) >= k2 ? r : r + 1;
 }
 
 // Bin layout of one partial: [0, nsh) E, [nsh, 2nsh) D, [2nsh, 3nsh) T,
 // then 3 x h one-dimensional energies, then totals E, eps, H, T, nonfinite.
-// Pass 1: every wavefront takes whole k_z rows (fixed k_x, k_y) in a grid-stride
-// loop, lanes along k_z, and adds into its own FP64 bins in LDS in a fixed order;
-// the block then sums its wavefronts' bins in wavefront order, so the spectra are
-// reproducible bit for bit.  Along a row the shell index does not decrease with
-// k_z, so a segmented shuffle scan leaves each shell's sum over the 64 lanes in
-// the segment's last lane, which adds it to the bin (the tails of one scan have
-// distinct shells); each lane owns its k_z bin; the row total goes to its k_x and
-// k_y bins from lane 0.
-template <typename R>
-__global__ void __launch_bounds__(1024)
+//
+// Pass 1.  The rows (k_x, k_y) = (+-a, +-b) and (+-b, +-a) share k_x^2 + k_y^2, so every
+// k_z of theirs lies in the same shell: a wavefront takes one pair a <= b and one chunk of
+// 64 k_z (lanes along k_z), adds its up to eight rows lane by lane, and sorts the sums
+// into shells once.  Along a row the shell index does not decrease with k_z, so a
+// segmented shuffle scan leaves each shell's sum over the 64 lanes in the segment's
+// last lane, which adds it to the wavefront's bin in LDS.  The k_z energy stays in the
+// lane's register (a wavefront keeps one chunk), the row totals go to their k_x and k_y
+// bins, and the k_z = N/2 entries of the rows are taken by eight lanes together.  Every
+// sum has a fixed order (pairs in a grid-stride loop, then wavefronts, then blocks), so
+// the spectra are reproducible bit for bit.
+//
+// Bound by the reads (every entry of the state is read, also outside the truncation, for
+// the count of non-finite ones).  With a scan and a set of bin updates per row, and a
+// chunk of one lane for k_z = N/2, it was bound by those LDS operations: a call with a
+// transfer field took 689 us at 384^3 FP32 (1.36 GB), now 305 us, 4.5 TB/s; 512^3 2309 -> 710
+// us, 256^3 FP64 261 -> 195 us; a plain copy reaches 4.9 to 6 TB/s.  Up to 96^3 a call is its
+// launches and the wait, about 40 us either way.
+//
+// Threads of a block at most: two fields of FP64 (96 loads of 16 bytes a lane) take more
+// than the 128 registers a block of 1024 threads leaves.
+template <typename R, bool NH>
+constexpr int spectra_threads() { return NH && sizeof(R) == 8 ? 512 : 1024; }
+template <typename R, bool NH>
+__global__ void __launch_bounds__((spectra_threads<R, NH>()))
 k_spectra(const Cx<R>* __restrict__ u, const Cx<R>* __restrict__ nh, double nu, int n, int h,
-          int nsh, long long comp, double* __restrict__ partials) {
+          int nsh, long long comp, int nchunks, double* __restrict__ partials) {
   extern __shared__ double bins_all[];
-  const int nb = 3 * nsh + 3 * h + 5;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwb = blockDim.x >> 6;
-  double* bins = bins_all + wave * nb;
-  for (int t = threadIdx.x; t < nwb * nb; t += blockDim.x) bins_all[t] = 0.0;
+  constexpr int KIND = NH ? 3 : 2;         // shell spectra with bins here
+  const int nw = spectra_wave_bins(n, nsh, NH);  // bins of a wavefront
+  const int lane = threadIdx.x & 63, nwb = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double* bins = bins_all + wave * nw;     // E, D(, T) by shell, E by |k_x|, by |k_y|
+  const int bx = KIND * nsh, by = bx + h, bz = by + h, bt = bz + 64;
+  for (int t = threadIdx.x; t < nwb * nw; t += blockDim.x) bins_all[t] = 0.0;
   __syncthreads();
-  double tE = 0, tD = 0, tH = 0, tT = 0;
+  const int half = n / 2;
+  const int npairs = (half + 1) * (half + 2) / 2;
+  const int w0 = blockIdx.x * nwb + wave, nwaves = gridDim.x * nwb;  // nwaves is a multiple of nchunks
+  const int chunk = w0 % nchunks, kz = chunk * 64 + lane;
+  const bool in = kz < half;
+  const double wz = kz == 0 ? 1.0 : 2.0;
+  double tE = 0, tD = 0, tH = 0, tT = 0, ez = 0;
   unsigned bad = 0;
-  const long long nrows = (long long)n * n;
-  const long long nwaves = (long long)gridDim.x * nwb;
-  for (long long row = (long long)blockIdx.x * nwb + wave; row < nrows; row += nwaves) {
-    const int yi = (int)(row % n), xi = (int)(row / n);
-    const int kx = kval(xi, n), ky = kval(yi, n);
-    double erow = 0.0;
-    for (int kz0 = 0; kz0 < h; kz0 += 64) {
-      const int kz = kz0 + lane;
-      const bool in = kz < h;
-      double e = 0.0, d = 0.0, t = 0.0;
-      int s = 0x7fffffff;  // lanes past the row end: a key above every shell
-      if (in) {
-        const long long idx = row * h + kz;
-        const double w = (kz == 0 || 2 * kz == n) ? 1.0 : 2.0;
-        const Cx<R> a0 = u[idx], a1 = u[comp + idx], a2 = u[2 * comp + idx];
-        const double ar[3] = {(double)a0.re, (double)a1.re, (double)a2.re};
-        const double ai[3] = {(double)a0.im, (double)a1.im, (double)a2.im};
-        bool fin = true;
-        for (int c = 0; c < 3; ++c) fin = fin && isfinite(ar[c]) && isfinite(ai[c]);
-        if (nh != nullptr) {
-          for (int c = 0; c < 3; ++c) {
-            const Cx<R> b = nh[c * comp + idx];
-            fin = fin && isfinite((double)b.re) && isfinite((double)b.im);
-            t += ar[c] * (double)b.re + ai[c] * (double)b.im;
-          }
-          t *= w;
-        }
-        const long long k2 = (long long)kx * kx + (long long)ky * ky + (long long)kz * kz;
-        s = shell_of(k2);  // kept for non-finite lanes too, so the keys stay sorted
-        if (!fin) {
-          ++bad;
-          t = 0.0;
-        } else {
-          e = 0.5 * w * (ar[0] * ar[0] + ai[0] * ai[0] + ar[1] * ar[1] + ai[1] * ai[1] +
-                         ar[2] * ar[2] + ai[2] * ai[2]);
-          d = 2.0 * nu * (double)k2 * e;
-          // helicity density: with u = a + i b, Re(conj(u).(i k x u)) = 2 k.(a x b), so
-          // 1/2 w Re(conj(u).omega) = w k.(a x b)
-          const double cxr = ar[1] * ai[2] - ar[2] * ai[1];
-          const double cyr = ar[2] * ai[0] - ar[0] * ai[2];
-          const double czr = ar[0] * ai[1] - ar[1] * ai[0];
-          tH += w * ((double)kx * cxr + (double)ky * cyr + (double)kz * czr);
-          tE += e;
-          tD += d;
-          tT += t;
-          erow += e;
-          bins[3 * nsh + 2 * h + kz] += e;
-        }
-      }
-      // an iteration whose contributions are all zero changes no shell bin (skipped)
-      if (__ballot(e != 0.0 || d != 0.0 || t != 0.0) == 0) continue;
-      // segmented inclusive scan over the lanes (keys s non-decreasing with the lane)
-      for (int off = 1; off < 64; off <<= 1) {
-        const double eu = __shfl_up(e, off), du = __shfl_up(d, off);
-        const int su = __shfl_up(s, off);
-        double tu = 0.0;
-        if (nh != nullptr) tu = __shfl_up(t, off);
-        if (lane >= off && su == s) {
-          e += eu;
-          d += du;
-          t += tu;
-        }
-      }
-      const int sn = __shfl_down(s, 1);
-      if (in && (lane == 63 || sn != s)) {
-        bins[s] += e;
-        bins[nsh + s] += d;
-        if (nh != nullptr) bins[2 * nsh + s] += t;
+  // energy 1/2 w |u|^2, transfer and helicity of one entry; zero if it is not finite
+  // helicity density: with u = a + i b, Re(conj(u).(i k x u)) = 2 k.(a x b), so
+  // 1/2 w Re(conj(u).omega) = w k.(a x b)
+  auto entry = [&](const Cx<R>* a, const Cx<R>* b, double w, double kx, double ky, double kzd, double& e, double& t) {
+    const double ar[3] = {(double)a[0].re, (double)a[1].re, (double)a[2].re};
+    const double ai[3] = {(double)a[0].im, (double)a[1].im, (double)a[2].im};
+    bool fin = true;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) fin = fin && isfinite(a[c].re) && isfinite(a[c].im);
+    double tt = 0.0;
+    if constexpr (NH) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        fin = fin && isfinite(b[c].re) && isfinite(b[c].im);
+        tt += ar[c] * (double)b[c].re + ai[c] * (double)b[c].im;
       }
     }
-    for (int off = 32; off > 0; off >>= 1) erow += __shfl_down(erow, off);
+    if (!fin) {
+      ++bad;
+      return;
+    }
+    e += 0.5 * w * (ar[0] * ar[0] + ai[0] * ai[0] + ar[1] * ar[1] + ai[1] * ai[1] + ar[2] * ar[2] + ai[2] * ai[2]);
+    t += w * tt;
+    const double cxr = ar[1] * ai[2] - ar[2] * ai[1];
+    const double cyr = ar[2] * ai[0] - ar[0] * ai[2];
+    const double czr = ar[0] * ai[1] - ar[1] * ai[0];
+    tH += w * (kx * cxr + ky * cyr + kzd * czr);
+  };
+  for (int p = w0 / nchunks; p < npairs; p += nwaves / nchunks) {
+    int b = (int)((sqrtf(8.0f * (float)p + 1.0f) - 1.0f) * 0.5f);  // b (b + 1) / 2 <= p, corrected below
+    while (b * (b + 1) / 2 > p) --b;
+    while ((b + 1) * (b + 2) / 2 <= p) ++b;
+    b = __builtin_amdgcn_readfirstlane(b);
+    const int a = p - b * (b + 1) / 2;                  // a <= b
+    const int na = (a == 0 || a == half) ? 1 : 2, nb = (b == 0 || b == half) ? 1 : 2;
+    double e2[2] = {0.0, 0.0}, t = 0.0, n2[2] = {0.0, 0.0}, tn = 0.0;
+    const int q = a * a + b * b;
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      if (g == 1 && a == b) break;
+      const int ka = g ? b : a, kb = g ? a : b, ca = g ? nb : na, cb = g ? na : nb;
+      Cx<R> va[4][3], vb[4][3];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int sx = r >> 1, sy = r & 1;
+        if (sx >= ca || sy >= cb) continue;
+        // the index of -k (k = N/2 has the one index N/2)
+        const int xi = sx ? n - ka : ka, yi = sy ? n - kb : kb;
+        const long long row = ((long long)xi * n + yi) * h;
+        const long long idx = row + (in ? kz : 0);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          va[r][c] = u[c * comp + idx];
+          if constexpr (NH) vb[r][c] = nh[c * comp + idx];
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int sx = r >> 1, sy = r & 1;
+        if (sx >= ca || sy >= cb) continue;
+        const double kx = (sx || ka == half) ? -(double)ka : (double)ka;
+        const double ky = (sy || kb == half) ? -(double)kb : (double)kb;
+        if (in) entry(va[r], vb[r], wz, kx, ky, (double)kz, e2[g], t);
+      }
+    }
+    if (chunk == nchunks - 1) {
+      // the k_z = N/2 entries: lanes 0..3 the rows of the first group, 4..7 of the second
+      const int g = lane >> 2, sx = (lane >> 1) & 1, sy = lane & 1;
+      const int ka = g ? b : a, kb = g ? a : b, ca = g ? nb : na, cb = g ? na : nb;
+      if (lane < 8 && sx < ca && sy < cb && !(g == 1 && a == b)) {
+        const int xi = sx ? n - ka : ka, yi = sy ? n - kb : kb;
+        const long long idx = ((long long)xi * n + yi) * h + half;
+        Cx<R> va[3], vb[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          va[c] = u[c * comp + idx];
+          if constexpr (NH) vb[c] = nh[c * comp + idx];
+        }
+        const double kx = (sx || ka == half) ? -(double)ka : (double)ka;
+        const double ky = (sy || kb == half) ? -(double)kb : (double)kb;
+        entry(va, vb, 1.0, kx, ky, (double)half, n2[g], tn);
+      }
+    }
+    double e = e2[0] + e2[1];
+    ez += e;
+    const int k2 = q + kz * kz;
+    double d = 2.0 * nu * (double)k2 * e;
+    tE += e;
+    tD += d;
+    tT += t;
+    // row totals: group 0 has |k_x| = a, |k_y| = b, group 1 the other way round
+    double r0 = e2[0] + n2[0], r1 = e2[1] + n2[1];
+    // a chunk whose contributions are all zero changes no bin
+    if (__ballot(r0 != 0.0 || r1 != 0.0 || t != 0.0 || tn != 0.0) == 0) continue;
+    for (int off = 32; off > 0; off >>= 1) {
+      r0 += __shfl_down(r0, off);
+      r1 += __shfl_down(r1, off);
+    }
     if (lane == 0) {
-      bins[3 * nsh + abs(kx)] += erow;
-      bins[3 * nsh + h + abs(ky)] += erow;
+      bins[bx + a] += r0;
+      bins[by + b] += r0;
+      bins[bx + b] += r1;
+      bins[by + a] += r1;
+    }
+    if (chunk == nchunks - 1) {
+      double en = n2[0] + n2[1];
+      for (int off = 4; off > 0; off >>= 1) {
+        en += __shfl_down(en, off);
+        if constexpr (NH) tn += __shfl_down(tn, off);
+      }
+      if (lane == 0) {
+        const int k2n = q + half * half, sn = shell_small(k2n);
+        const double dn = 2.0 * nu * (double)k2n * en;
+        bins[sn] += en;
+        bins[nsh + sn] += dn;
+        if constexpr (NH) bins[2 * nsh + sn] += tn;
+        bins[bt] += en;  // E_z at N/2
+        tE += en;
+        tD += dn;
+        tT += tn;
+      }
+    }
+    // segmented inclusive scan over the lanes (keys s non-decreasing with the lane; lanes
+    // past the row end carry a key above every shell and zeros)
+    const int s = in ? shell_small(k2) : 0x7fffffff;
+    for (int off = 1; off < 64; off <<= 1) {
+      const double eu = __shfl_up(e, off), du = __shfl_up(d, off);
+      const int su = __shfl_up(s, off);
+      double tu = 0.0;
+      if constexpr (NH) tu = __shfl_up(t, off);
+      if (lane >= off && su == s) {
+        e += eu;
+        d += du;
+        t += tu;
+      }
+    }
+    const int sn = __shfl_down(s, 1);
+    if (in && (lane == 63 || sn != s)) {
+      bins[s] += e;
+      bins[nsh + s] += d;
+      if constexpr (NH) bins[2 * nsh + s] += t;
     }
   }
   for (int off = 32; off > 0; off >>= 1) {
@@ -117,19 +217,28 @@ k_spectra(const Cx<R>* __restrict__ u, const Cx<R>* __restrict__ nh, double nu, 
     tT += __shfl_down(tT, off);
     bad += __shfl_down(bad, off);
   }
-  const int tot = 3 * nsh + 3 * h;
+  bins[bz + lane] = ez;
   if (lane == 0) {
-    bins[tot + 0] = tE;
-    bins[tot + 1] = tD;
-    bins[tot + 2] = tH;
-    bins[tot + 3] = tT;
-    bins[tot + 4] = (double)bad;
+    bins[bt + 1] = tE;
+    bins[bt + 2] = tD;
+    bins[bt + 3] = tH;
+    bins[bt + 4] = tT;
+    bins[bt + 5] = (double)bad;
   }
   __syncthreads();
-  double* out = partials + (long long)blockIdx.x * nb;
-  for (int t = threadIdx.x; t < nb; t += blockDim.x) {
+  // the block's partial, in the common layout; E_z of chunk c from the wavefronts that keep it
+  const int nb_out = 3 * nsh + 3 * h + 5;
+  double* out = partials + (long long)blockIdx.x * nb_out;
+  for (int t = threadIdx.x; t < nb_out; t += blockDim.x) {
+    const int y = t - 3 * nsh, z = y - 2 * h, tot = y - 3 * h;
     double acc = 0.0;
-    for (int w = 0; w < nwb; ++w) acc += bins_all[w * nb + t];
+    if (z >= 0 && tot < 0 && z < half) {
+      for (int w = 0; w < nwb; ++w)
+        if ((blockIdx.x * nwb + w) % nchunks == z / 64) acc += bins_all[w * nw + bz + z % 64];
+    } else if (y >= 0 || t < KIND * nsh) {
+      const int from = y < 0 ? t : (tot >= 0 ? bt + 1 + tot : (z >= 0 ? bt : bx + y));
+      for (int w = 0; w < nwb; ++w) acc += bins_all[w * nw + from];
+    }
     out[t] = acc;
   }
 }

@@ -750,6 +750,35 @@ ns_status vjp_t(ns_ctx* c, const void* u0v, void* lamv, double dt, int variant, 
   return NS_OK;
 }
 
+// Both passes of the spectra reduction; the partials hold kSpecBlocks bin sets.
+template <typename R>
+hipError_t launch_spectra(const Cx<R>* u, const Cx<R>* nh, double nu, int n, double* partials, double* out,
+                          hipStream_t stream) {
+  const int h = n / 2 + 1, nsh = num_shells(n), nbins = 3 * nsh + 3 * h + 5;
+  const int nchunks = (n / 2 + 63) / 64, npairs = h * (h + 1) / 2;
+  // wavefronts per block: as many bin sets as fit in 156 KB of LDS, up to the kernel's
+  // limit, and no more than there are pairs of rows for; the wavefronts of the grid divide
+  // into chunks
+  const size_t set = (size_t)ns::spectra_wave_bins(n, nsh, nh != nullptr) * sizeof(double);
+  const int limit = (nh != nullptr ? ns::spectra_threads<R, true>() : ns::spectra_threads<R, false>()) / 64;
+  const int most = (int)std::max<size_t>(1, std::min<size_t>(limit, (size_t)(156 * 1024) / set));
+  const int nwb = std::min(most, (npairs * nchunks + kSpecBlocks - 1) / kSpecBlocks);
+  int nblocks = std::min(kSpecBlocks, (npairs * nchunks + nwb - 1) / nwb);
+  nblocks = std::max(nchunks, nblocks / nchunks * nchunks);
+  const size_t lds = nwb * set;
+  auto run = [&](auto kernel) -> hipError_t {
+    hipError_t e = allow_lds(kernel, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(64 * nwb), lds, stream, u, nh, nu, n, h, nsh,
+                       (long long)n * n * h, nchunks, partials);
+    return hipSuccess;
+  };
+  const hipError_t e = nh != nullptr ? run(ns::k_spectra<R, true>) : run(ns::k_spectra<R, false>);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(ns::k_spectra_sum, dim3((nbins + 7) / 8), dim3(256), 0, stream, partials, nblocks, nbins, out);
+  return hipSuccess;
+}
+
 // Enqueue the reduction and its copy into pinned host memory, then record an
 // event: the result can be waited for without waiting for later work.
 template <typename R>
@@ -767,17 +796,9 @@ ns_status spectra_enqueue_t(ns_ctx* c, const void* u, const void* nh) {
   if (c->spec_ev == nullptr &&
       (st = hip_check(c, hipEventCreateWithFlags(&c->spec_ev, hipEventDisableTiming), "spectra event")) != NS_OK)
     return st;
-  // wavefronts per block: up to 16, as many private bin sets as fit in 128 KB of LDS
-  const size_t set = (size_t)l.nbins * sizeof(double);
-  const int nwb = (int)std::max<size_t>(1, std::min<size_t>(16, (size_t)(128 * 1024) / set));
-  const size_t lds = nwb * set;
-  hipError_t e = allow_lds(ns::k_spectra<R>, lds);
+  hipError_t e = launch_spectra<R>(static_cast<const Cx<R>*>(u), static_cast<const Cx<R>*>(nh), c->cfg.nu, l.g.n,
+                                   p.spec, p.specout, c->stream);
   if (e != hipSuccess) return hip_check(c, e, "k_spectra attribute");
-  hipLaunchKernelGGL(ns::k_spectra<R>, dim3(kSpecBlocks), dim3(64 * nwb), lds, c->stream,
-                     static_cast<const Cx<R>*>(u), static_cast<const Cx<R>*>(nh), c->cfg.nu, l.g.n,
-                     l.g.h, l.nsh, l.g.comp, p.spec);
-  hipLaunchKernelGGL(ns::k_spectra_sum, dim3((l.nbins + 7) / 8), dim3(256), 0, c->stream, p.spec,
-                     kSpecBlocks, l.nbins, p.specout);
   if ((st = hip_check(c, hipGetLastError(), "spectra launch")) != NS_OK) return st;
   if ((st = hip_check(c, hipMemcpyAsync(c->pin_spec, p.specout, l.nbins * sizeof(double),
                                         hipMemcpyDeviceToHost, c->stream), "spectra copy")) != NS_OK)
@@ -1098,14 +1119,9 @@ ns_status spectra_static_t(int n, double nu, const void* u, const void* nh, hipS
   double* partials = base;
   double* bins = base + (size_t)kSpecBlocks * nbins;
   const size_t set = (size_t)nbins * sizeof(double);
-  const int nwb = (int)std::max<size_t>(1, std::min<size_t>(16, (size_t)(128 * 1024) / set));
-  const size_t lds = nwb * set;
-  hipError_t e = allow_lds(ns::k_spectra<R>, lds);
+  hipError_t e = launch_spectra<R>(static_cast<const Cx<R>*>(u), static_cast<const Cx<R>*>(nh), nu, n, partials, bins,
+                                   stream);
   if (e != hipSuccess) return hip_check(nullptr, e, "k_spectra attribute");
-  hipLaunchKernelGGL(ns::k_spectra<R>, dim3(kSpecBlocks), dim3(64 * nwb), lds, stream, static_cast<const Cx<R>*>(u),
-                     static_cast<const Cx<R>*>(nh), nu, n, h, nsh, (long long)n * n * h, partials);
-  hipLaunchKernelGGL(ns::k_spectra_sum, dim3((nbins + 7) / 8), dim3(256), 0, stream, partials, kSpecBlocks, nbins,
-                     bins);
   if ((st = hip_check(nullptr, hipGetLastError(), "spectra launch")) != NS_OK) return st;
   double host[static_nbins(kStaticMaxN)];  // on the stack: no host allocation either
   if ((st = hip_check(nullptr, hipMemcpyAsync(host, bins, set, hipMemcpyDeviceToHost, stream), "spectra copy")) !=
