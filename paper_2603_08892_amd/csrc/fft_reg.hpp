@@ -183,9 +183,31 @@ struct StageMap {
   __device__ __forceinline__ static bool ok(int t, int b) { return FULL || t + TPL * b < N / R; }
 };
 
+// Twiddles: KEPT = false reads each from the table tw[] (in LDS) where it is used; true
+// takes them from the registers that load_twiddles filled, tw[i] in the order of use.
 template <int N, int TPL, int S, int NS, int R, int... Rest>
 struct RegStages {
-  template <bool WAVE, typename T, int ES>
+  // twiddles a thread uses in this stage and the ones after it
+  static constexpr int twiddles() {
+    const int own = NS > 1 ? StageMap<N, TPL, R>::NB * (R - 1) : 0;
+    if constexpr (sizeof...(Rest) > 0) return own + RegStages<N, TPL, S, NS * R, Rest...>::twiddles();
+    else return own;
+  }
+  template <typename T>
+  __device__ __forceinline__ static void load_twiddles(Cx<T>* w, int t, const Cx<T>* tw) {
+    constexpr int NB = StageMap<N, TPL, R>::NB;
+    if constexpr (NS > 1) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const int k = (t + TPL * b) % NS;  // (of a butterfly that does not exist: unused, in range)
+#pragma unroll
+        for (int m = 1; m < R; ++m) w[b * (R - 1) + m - 1] = tw[k * m * (N / (NS * R))];
+      }
+    }
+    if constexpr (sizeof...(Rest) > 0)
+      RegStages<N, TPL, S, NS * R, Rest...>::load_twiddles(w + (NS > 1 ? NB * (R - 1) : 0), t, tw);
+  }
+  template <bool WAVE, bool KEPT, typename T, int ES>
   __device__ __forceinline__ static void run(Cx<T>* v, int t, const LineView<T, ES>& lv, const Cx<T>* tw) {
     using M = StageMap<N, TPL, R>;
     constexpr int NB = M::NB;
@@ -194,10 +216,10 @@ struct RegStages {
       if (!M::ok(t, b)) continue;
       const int j = t + TPL * b;
       if constexpr (NS > 1) {
-        const int k = j % NS;
+        [[maybe_unused]] const int k = j % NS;
 #pragma unroll
         for (int m = 1; m < R; ++m) {
-          const Cx<T> w = tw[k * m * (N / (NS * R))];
+          const Cx<T> w = KEPT ? tw[b * (R - 1) + m - 1] : tw[k * m * (N / (NS * R))];
           v[b * R + m] = (S < 0) ? cmul(v[b * R + m], w) : cmulc(v[b * R + m], w);
         }
       }
@@ -224,7 +246,8 @@ struct RegStages {
 #pragma unroll
         for (int m = 0; m < R2; ++m) v[b * R2 + m] = lv.at(j + m * (N / R2));
       }
-      RegStages<N, TPL, S, NS * R, Rest...>::template run<WAVE>(v, t, lv, tw);
+      RegStages<N, TPL, S, NS * R, Rest...>::template run<WAVE, KEPT>(
+          v, t, lv, KEPT && NS > 1 ? tw + NB * (R - 1) : tw);
     }
   }
   template <int F, int... X>
@@ -292,10 +315,28 @@ struct RegFft<N, TPL, S, Radices<Rs...>> {
   // tables of the line (the value of such a register is never used)
   __device__ __forceinline__ static int in_at(int t, int i) { return in_ok(t, i) ? in_pos(t, i) : 0; }
   __device__ __forceinline__ static int out_at(int t, int i) { return out_ok(t, i) ? out_pos(t, i) : 0; }
+  static constexpr int TWIDDLES = RegStages<N, TPL, S, 1, Rs...>::twiddles();
   template <bool WAVE = false, typename T, int ES>
   __device__ __forceinline__ static void run(Cx<T>* v, int t, const LineView<T, ES>& lv, const Cx<T>* tw) {
     static_assert(!WAVE || TPL <= 64, "a wavefront-local line fits in one wavefront");
-    RegStages<N, TPL, S, 1, Rs...>::template run<WAVE>(v, t, lv, tw);
+    RegStages<N, TPL, S, 1, Rs...>::template run<WAVE, false>(v, t, lv, tw);
+  }
+  // The twiddles of this thread, for several transforms: kept in registers (KEEP) or
+  // read from the table by each of them.
+  template <typename T, bool KEEP>
+  struct Twiddles {
+    Cx<T> w[KEEP && TWIDDLES > 0 ? TWIDDLES : 1];
+    const Cx<T>* table;
+    // tw: the table in LDS, complete and visible to this thread
+    __device__ __forceinline__ Twiddles(int t, const Cx<T>* tw) : table(tw) {
+      if constexpr (KEEP) RegStages<N, TPL, S, 1, Rs...>::load_twiddles(w, t, tw);
+    }
+  };
+  template <bool WAVE = false, typename T, int ES, bool KEEP>
+  __device__ __forceinline__ static void run(Cx<T>* v, int t, const LineView<T, ES>& lv,
+                                             const Twiddles<T, KEEP>& tw) {
+    static_assert(!WAVE || TPL <= 64, "a wavefront-local line fits in one wavefront");
+    RegStages<N, TPL, S, 1, Rs...>::template run<WAVE, KEEP>(v, t, lv, KEEP ? tw.w : tw.table);
   }
 };
 

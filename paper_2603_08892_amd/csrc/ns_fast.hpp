@@ -73,6 +73,27 @@ __device__ __forceinline__ Cx<T> ld_masked(const Cx<T>* __restrict__ base, uint3
   return cx(v.re * m, v.im * m);
 }
 
+// Masked loads through a buffer descriptor: an offset past its end reads zero without
+// touching memory, so a masked element costs a select on the offset and no arithmetic,
+// and every load of a thread can be issued before the first use.
+using BufDesc = __amdgpu_buffer_rsrc_t;
+__device__ __forceinline__ BufDesc buf_desc(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00027000);
+}
+template <typename T>
+__device__ __forceinline__ Cx<T> ld_buf(BufDesc b, uint32_t off, bool ok) {
+  const uint32_t byte = ok ? off * (uint32_t)sizeof(Cx<T>) : 0x80000000u;  // fields are below 2 GiB (TypedPlan)
+  Cx<T> v;
+  if constexpr (sizeof(T) == 4) {
+    const auto w = __builtin_amdgcn_raw_buffer_load_b64(b, (int)byte, 0, 0);
+    __builtin_memcpy(&v, &w, sizeof(v));
+  } else {
+    const auto w = __builtin_amdgcn_raw_buffer_load_b128(b, (int)byte, 0, 0);
+    __builtin_memcpy(&v, &w, sizeof(v));
+  }
+  return v;
+}
+
 // Truncation test along one k_x line (fixed k_y, k_z) in 32-bit arithmetic
 // (|k_i| <= N/2 <= 256 here, so |k|^2 < 2^18): every mask is k_x^2 <= hi2 and
 // |k_x| <= xmax with per-line thresholds (xmax from the pair conditions of
@@ -113,9 +134,22 @@ struct TypedPlan {
   static constexpr int TPL = TPL_;
   static constexpr int L = tile_cols<T>();
   static constexpr int LP = L + 1;
-  static_assert((unsigned long long)sizeof(Cx<T>) * N * N * (N / 2 + 1) < (1ull << 32),
-                "32-bit byte offsets need sizeof(complex) N^2 (N/2+1) < 2^32");
+  // (k_z pitch of a scratch field: at most N/2 rounded up to the tile)
+  static_assert((unsigned long long)sizeof(Cx<T>) * N * N * ((N / 2 + L) / L * L) <= (1ull << 31),
+                "32-bit byte offsets and buffer descriptors need fields of at most 2 GiB");
   static constexpr int EPT = Inv_::template ept<N_, TPL_>();
+  // z passes (f_zcross): whether the twiddles stay in registers, and how many slices ahead
+  // a slice is loaded.  The pass is bound by its waves per SIMD and by LDS traffic: kept
+  // twiddles take a quarter of the LDS reads away, a deeper prefetch hides the loads,
+  // both cost registers.  Best of the six combinations, z pass in us (twiddles kept or not /
+  // slices ahead): 4 registers a transform, 256^3 kept/2 113.7, kept/1 119.9, not/2 120.1; 8
+  // or 9 over 32 threads, 192^3 kept/0 43.6, kept/1 47.1, not/1 45.4 and 160^3, 216^3
+  // likewise (four waves instead of three); 8 or 9 over 64, 512^3 not/1 825, kept/0 843, kept/1
+  // 871 and 324^3, 384^3 likewise; others kept/1 (128^3 18.1 against 18.7 kept/0, 20.1 not/2;
+  // 360^3 450 against 458 to 493; 64^3, 8 threads, kept/2 8.3 against 8.5).
+  static constexpr int ZREGS = EPT * (int)sizeof(T) / 4;  // 32-bit register pairs a transform
+  static constexpr bool KEEP = !(TPL == 64 && ZREGS > 4);
+  static constexpr int AHEAD = ZREGS <= 4 || TPL <= 8 ? 2 : (TPL == 32 && ZREGS <= 9) ? 0 : 1;
   static_assert(EPT == Fwd_::template ept<N_, TPL_>(), "both directions hold the same registers");
   using Inv = Inv_;   // radices of the inverse transforms
   using Fwd = Fwd_;   // radices of the forward transforms (reverse order of Inv)
@@ -124,7 +158,6 @@ template <int N, int TPL, typename Inv, typename Fwd>
 struct LinePlan : TypedPlan<float, N, TPL, Inv, Fwd> {};
 template <int N, int TPL, typename Inv, typename Fwd>
 struct LinePlanD : TypedPlan<double, N, TPL, Inv, Fwd> {};
-
 // Plans of the five passes of one size; PZ = lines per block of the z pass; the
 // adjoint z pass (five inverse and three forward slices) may take its own plan ZA
 // with PZA lines per block.  YC: the step sequences run f_xinv<XI, false> and
@@ -381,7 +414,17 @@ f_ycurl(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__
 // from the half spectra on the fly (Z(k) = a(k) + i b(k), Z(N-k) = conj a(k) + i conj b(k),
 // imaginary parts of the k_z = 0 and N/2 coefficients dropped); the product
 // f = u x omega stays in registers; forward slices (f_x + i f_y) and f_z; the
-// spectra are split through LDS.  Output scratch fields 0, 1, 2 = f_x, f_y, f_z (unnormalised).
+// spectrum of f_x + i f_y is split with its mirror through the line's LDS buffer, f_z goes
+// out from the registers.  Output scratch fields 0, 1, 2 = f_x, f_y, f_z (unnormalised).
+//
+// Bound by LDS and by instruction issue at the large sizes (512^3: 180 LDS and 1,330 vector
+// instructions a wavefront), by HBM at 256^3 (604 MB in 114 us, 5.3 TB/s, what a plain
+// copy reaches).  What the pass does without: twiddles read once a thread instead of
+// once a transform where they fit, masks as out-of-range buffer loads instead of a
+// multiplication, no division and no block barrier in the output.  Against the pass
+// before, z pass in us: 128^3 20.3 -> 18.3, 160^3 40.8 -> 34.9, 192^3 50.7 -> 44.4, 216^3 85.1 ->
+// 71.4, 256^3 126.7 -> 114.3, 270^3 207 -> 166, 512^3 (C_t = 2/3) 944 -> 829; 324^3, 360^3 and
+// 384^3 2-4% less.
 template <typename C, int P>
 __global__ void __launch_bounds__(P * C::TPL)
 f_zcross(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ twg, Geom g) {
@@ -390,50 +433,53 @@ f_zcross(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict_
   using FI = RegFft<N, TPL, +1, typename C::Inv>;
   using FF = RegFft<N, TPL, -1, typename C::Fwd>;
   static_assert(FI::RL == FF::R0, "the forward transform must start with the last inverse radix");
+  static_assert(64 % TPL == 0, "a line inside one wavefront");
   constexpr int LP = line_pitch(N);
   __shared__ Cx<T> tw[N];
-  __shared__ Cx<T> xb[P * LP];  // exchanges, then the spectrum of f_z
-  __shared__ Cx<T> sp[P * N];   // spectrum of f_x + i f_y
+  __shared__ Cx<T> xb[P * LP];
   const int tid = threadIdx.x;
   const int p = tid / TPL, t = tid % TPL;
-  // a line's threads within one wavefront synchronise at wavefront scope; a line
-  // that straddles wavefronts (TPL not dividing 64) uses block barriers
-  constexpr bool WV = (64 % TPL == 0);
-  const uint32_t line0 = (uint32_t)blockIdx.x * P;
-  for (int i = tid; i < N; i += NT) tw[i] = twg[i];
-  __syncthreads();  // the line transforms below synchronise only within a wavefront
+  const uint32_t line = (uint32_t)blockIdx.x * P + p;
   const LineView<T, 1> lv{xb + p * LP};
-  const uint32_t lbase = (line0 + p) * (uint32_t)g.kzp;
+  const uint32_t lbase = line * (uint32_t)g.kzp;
+  const uint32_t fbytes = (uint32_t)(g.wcomp * (long long)sizeof(Cx<T>));
   T fx[EPT], fy[EPT], fz[EPT];
   Cx<T> z[2][EPT];
   Cx<T> v[EPT];
-  // raw half-spectrum pairs of the slices, loaded two slices ahead so that the
-  // loads overlap the transforms (the barriers inside a transform keep the
-  // compiler from moving later loads above it)
-  Cx<T> ra[2][EPT], rb[2][EPT];
+  // raw half-spectrum pairs of the slices, loaded AHEAD slices ahead so that the loads
+  // overlap the transforms (the barriers inside a transform keep the compiler from
+  // moving later loads above it)
+  Cx<T> ra[C::AHEAD > 1 ? 2 : 1][EPT], rb[C::AHEAD > 1 ? 2 : 1][EPT];
   auto fetch = [&](int q, Cx<T>* a, Cx<T>* b) {
+    const BufDesc da = buf_desc(W + (2 * q) * g.wcomp, fbytes), db = buf_desc(W + (2 * q + 1) * g.wcomp, fbytes);
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
       const int pos = FI::in_at(t, i);
       const int k = pos <= HN ? pos : N - pos;
-      a[i] = ld_masked(W + (2 * q) * g.wcomp, lbase + k, k < g.kzn);
-      b[i] = ld_masked(W + (2 * q + 1) * g.wcomp, lbase + k, k < g.kzn);
+      a[i] = ld_buf<T>(da, lbase + k, k < g.kzn);
+      b[i] = ld_buf<T>(db, lbase + k, k < g.kzn);
     }
   };
-  fetch(0, ra[0], rb[0]);
-  fetch(1, ra[1], rb[1]);
+  constexpr int AHEAD = C::AHEAD;
+  if (AHEAD > 0) fetch(0, ra[0], rb[0]);
+  if (AHEAD > 1) fetch(1, ra[1], rb[1]);
+  for (int i = tid; i < N; i += NT) tw[i] = twg[i];
+  __syncthreads();  // the line transforms below synchronise only within a wavefront
+  const typename FI::template Twiddles<T, C::KEEP> twi(t, tw);
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
+    constexpr int RING = AHEAD > 1 ? 2 : 1;
+    if (AHEAD == 0) fetch(q, ra[0], rb[0]);
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
       const int pos = FI::in_at(t, i);
-      const Cx<T> a = ra[q & 1][i], bb = rb[q & 1][i];
+      const Cx<T> a = ra[q % RING][i], bb = rb[q % RING][i];
       if (pos == 0 || pos == HN) v[i] = cx(a.re, bb.re);
       else if (pos < HN) v[i] = cx(a.re - bb.im, a.im + bb.re);
       else v[i] = cx(a.re + bb.im, bb.re - a.im);
     }
-    if (q == 0) fetch(2, ra[0], rb[0]);
-    FI::template run<WV>(v, t, lv, tw);
+    if (AHEAD > 0 && q + AHEAD < 3) fetch(q + AHEAD, ra[q % RING], rb[q % RING]);
+    FI::template run<true>(v, t, lv, twi);
     if (q < 2) {
 #pragma unroll
       for (int i = 0; i < EPT; ++i) z[q][i] = v[i];
@@ -447,27 +493,36 @@ f_zcross(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict_
     fy[i] = uz * wx - ux * wz;
     fz[i] = ux * wy - uy * wx;
   }
+  const typename FF::template Twiddles<T, C::KEEP> twf(t, tw);
 #pragma unroll
   for (int i = 0; i < EPT; ++i) v[i] = cx(fx[i], fy[i]);
-  FF::template run<WV>(v, t, lv, tw);
+  FF::template run<true>(v, t, lv, twf);
+  // split f_x + i f_y: the register holds k, the mirror N - k comes from the line's
+  // buffer; only registers that can hold k < kzn <= N/2 (kzn <= N/2: every truncation
+  // leaves the Nyquist plane out)
+  exchange_barrier<true>();
 #pragma unroll
   for (int i = 0; i < EPT; ++i)
-    if (FF::out_ok(t, i)) sp[p * N + FF::out_pos(t, i)] = v[i];
+    if (FF::out_ok(t, i)) lv.at(FF::out_pos(t, i)) = v[i];
+  exchange_barrier<true>();
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    if ((i % FF::RL) * (N / FF::RL) >= HN) continue;  // out_pos >= N/2 for every thread
+    const int k = FF::out_pos(t, i);
+    if (FF::out_ok(t, i) && k < g.kzn) {
+      const Cx<T> c1 = v[i], c2 = lv.at(k == 0 ? 0 : N - k);
+      st_off<stream_stores<T>(N)>(W, lbase + k, cx(T(0.5) * (c1.re + c2.re), T(0.5) * (c1.im - c2.im)));
+      st_off<stream_stores<T>(N)>(W + g.wcomp, lbase + k, cx(T(0.5) * (c1.im + c2.im), T(-0.5) * (c1.re - c2.re)));
+    }
+  }
 #pragma unroll
   for (int i = 0; i < EPT; ++i) v[i] = cx(fz[i], T(0));
-  FF::template run<WV>(v, t, lv, tw);
-  __syncthreads();
+  FF::template run<true>(v, t, lv, twf);
 #pragma unroll
-  for (int i = 0; i < EPT; ++i)
-    if (FF::out_ok(t, i)) xb[p * LP + FF::out_pos(t, i)] = v[i];
-  __syncthreads();
-  for (int idx = tid; idx < P * g.kzn; idx += NT) {
-    const int k = idx % g.kzn, pp = idx / g.kzn;
-    const Cx<T> c1 = sp[pp * N + k], c2 = sp[pp * N + ((N - k) % N)];
-    const uint32_t off = (line0 + pp) * (uint32_t)g.kzp + k;
-    st_off<stream_stores<T>(N)>(W, off, cx(T(0.5) * (c1.re + c2.re), T(0.5) * (c1.im - c2.im)));
-    st_off<stream_stores<T>(N)>(W + g.wcomp, off, cx(T(0.5) * (c1.im + c2.im), T(-0.5) * (c1.re - c2.re)));
-    st_off<stream_stores<T>(N)>(W + 2 * g.wcomp, off, xb[pp * LP + k]);
+  for (int i = 0; i < EPT; ++i) {
+    if ((i % FF::RL) * (N / FF::RL) >= HN) continue;
+    const int k = FF::out_pos(t, i);
+    if (FF::out_ok(t, i) && k < g.kzn) st_off<stream_stores<T>(N)>(W + 2 * g.wcomp, lbase + k, v[i]);
   }
 }
 
