@@ -150,6 +150,15 @@ struct TypedPlan {
   static constexpr int ZREGS = EPT * (int)sizeof(T) / 4;  // 32-bit register pairs a transform
   static constexpr bool KEEP = !(TPL == 64 && ZREGS > 4);
   static constexpr int AHEAD = ZREGS <= 4 || TPL <= 8 ? 2 : (TPL == 32 && ZREGS <= 9) ? 0 : 1;
+  // x-forward passes (f_xfwd): points a chunk of stage operands, for stages with one
+  // operand and with two.  Small chunks, the next one loaded while one is used, keep a
+  // thread at fewer registers.  Two operands: one point a chunk (one or two at EPT over
+  // 12 or 16 threads a line: a quarter) brings 512-thread tiles to 128 registers and two
+  // tiles to a CU, or takes the spills away (chained RK4 stages, us, against half the
+  // points a chunk: 256^3 94.1 -> 78.7, 216^3 67.8 -> 51.5, 360^3 280 -> 255, 512^3 781 -> 661).  One
+  // operand: all points at once unless the plan says otherwise (XPass).
+  static constexpr int CHUNK_ONE = EPT;
+  static constexpr int CHUNK_TWO = TPL == 32 && EPT <= 12 ? 1 : (EPT + 3) / 4;
   static_assert(EPT == Fwd_::template ept<N_, TPL_>(), "both directions hold the same registers");
   using Inv = Inv_;   // radices of the inverse transforms
   using Fwd = Fwd_;   // radices of the forward transforms (reverse order of Inv)
@@ -158,6 +167,15 @@ template <int N, int TPL, typename Inv, typename Fwd>
 struct LinePlan : TypedPlan<float, N, TPL, Inv, Fwd> {};
 template <int N, int TPL, typename Inv, typename Fwd>
 struct LinePlanD : TypedPlan<double, N, TPL, Inv, Fwd> {};
+// An x plan whose one-operand stages take chunks of ONE points (TypedPlan::CHUNK_ONE).
+// PS-RK2 random steps, a quarter of the points against all: 216^3 590 against 625 us, 240^3
+// 758 against 800, 512^3 7.80 against 8.18 ms (fewer registers: two tiles a CU, no spills);
+// 144^3 164 against 165; at 256, 324, 360 and 384 1-2% slower, so those keep all.
+template <typename P, int ONE>
+struct XPass : P {
+  static constexpr int CHUNK_ONE = ONE;
+};
+
 // Plans of the five passes of one size; PZ = lines per block of the z pass; the
 // adjoint z pass (five inverse and three forward slices) may take its own plan ZA
 // with PZA lines per block.  YC: the step sequences run f_xinv<XI, false> and
@@ -220,7 +238,7 @@ f_xinv(const Cx<typename C::T>* __restrict__ S, Lay ls, Cx<typename C::T>* __res
   const LineView<T, C::LP> lv{xb + l};
   const uint32_t sbase = (uint32_t)(yi * ls.pitch + kz0) + l, sstep = (uint32_t)(N * ls.pitch);
   [[maybe_unused]] const T kyf = T(ky), kzf = T(kz);
-  Cx<T> ux[EPT], uy[EPT], uz[EPT], dy[EPT], dz[EPT];
+  Cx<T> ux[EPT], uy[EPT], uz[EPT], v[EPT];
   {
     bool ok[EPT];
     uint32_t idx[EPT];
@@ -247,9 +265,6 @@ f_xinv(const Cx<typename C::T>* __restrict__ S, Lay ls, Cx<typename C::T>* __res
       uy[i] = cmul(uy[i], phi);
       uz[i] = cmul(uz[i], phi);
     }
-    const T kxf = T(kval(p, N));
-    dy[i] = mul_i(scale(uy[i], kxf));
-    dz[i] = mul_i(scale(uz[i], kxf));
   }
   const uint32_t obase = (uint32_t)(yi * g.kzp + kz0) + l, ostep = (uint32_t)(N * g.kzp);
   auto store = [&](int f, const Cx<T>* v) {
@@ -260,6 +275,24 @@ f_xinv(const Cx<typename C::T>* __restrict__ S, Lay ls, Cx<typename C::T>* __res
           st_off<stream_stores<T>(N)>(W + f * g.wcomp, (uint32_t)F::out_pos(t, i) * ostep + obase, v[i]);
     }
   };
+  F::run(ux, t, lv, tw);
+  store(0, ux);
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) v[i] = mul_i(scale(uz[i], T(kval(F::in_at(t, i), N))));
+  F::run(v, t, lv, tw);  // D_z
+  if constexpr (CURL) {
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) v[i] = mul_i(scale(ux[i], kzf)) - v[i];  // omega_y
+  }
+  store(4, v);
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) v[i] = mul_i(scale(uy[i], T(kval(F::in_at(t, i), N))));
+  F::run(v, t, lv, tw);  // D_y
+  if constexpr (CURL) {
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) v[i] = v[i] - mul_i(scale(ux[i], kyf));  // omega_z
+  }
+  store(5, v);
   F::run(uy, t, lv, tw);
   store(1, uy);
   F::run(uz, t, lv, tw);
@@ -269,20 +302,6 @@ f_xinv(const Cx<typename C::T>* __restrict__ S, Lay ls, Cx<typename C::T>* __res
     for (int i = 0; i < EPT; ++i) uy[i] = mul_i(scale(uz[i], kyf) - scale(uy[i], kzf));  // omega_x
     store(3, uy);
   }
-  F::run(ux, t, lv, tw);
-  store(0, ux);
-  F::run(dz, t, lv, tw);
-  if constexpr (CURL) {
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) dz[i] = mul_i(scale(ux[i], kzf)) - dz[i];  // omega_y
-  }
-  store(4, dz);
-  F::run(dy, t, lv, tw);
-  if constexpr (CURL) {
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) dy[i] = dy[i] - mul_i(scale(ux[i], kyf));  // omega_z
-  }
-  store(5, dy);
 }
 
 // ------------------------------------------------------------------ y passes (in place)
@@ -568,12 +587,9 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
   const LineView<T, C::LP> lv{xb + l};
   Cx<T> r[3][EPT];
   Cx<T> phyz = cx(T(1), T(0));
-  // stage operands, read per chunk of points before that chunk's stores (out0 may
-  // alias an operand, which keeps the compiler from hoisting loads above stores):
-  // half of the points per chunk for two-operand stages, and for one-operand
-  // stages at N <= 128 (fewer registers, four waves per SIMD instead of three;
-  // measured faster there, slower at N = 256); the first chunk is read before the
-  // last transform so that its latency overlaps it
+  // stage operands, read a chunk of points ahead of the chunk whose outputs are stored
+  // (out0 may alias an operand, but only at the same point, so the next chunk's loads may
+  // go before this chunk's stores); the first chunk is read before the last transform
   const int op = OP == OP_ANY ? a.op : OP;
   [[maybe_unused]] const int feed = FEED == FEED_ANY ? a.feed : FEED;
   constexpr bool may0 = OP == OP_ANY || op_reads0(OP), may1 = OP == OP_ANY || op_reads1(OP);
@@ -588,31 +604,33 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
 #pragma unroll
       for (int i = 0; i < EPT; ++i) nx[c][i] = cx(T(0), T(0));
   }
-  constexpr int CH = ((may0 && may1) || ((may0 || may1) && N <= 128)) ? (EPT + 1) / 2 : EPT;
+  constexpr int CH = may0 && may1 ? C::CHUNK_TWO : C::CHUNK_ONE;  // points a chunk
+  constexpr int NBUF = CH < EPT ? 2 : 1;
   const LineTest keep = line_test(g, ky, kz);
   const bool line_kept = active && kz < g.kzn;
   // streaming stores into the compact stage buffers only (rows of whole 128-byte lines)
   const bool st0 = stream_stores<T>(N) && a.lo0.pitch == g.kzp;
   [[maybe_unused]] const bool st1 = stream_stores<T>(N) && a.lo1.pitch == g.kzp;
-  Cx<T> s0v[may0 ? 3 : 1][may0 ? CH : 1], s1v[may1 ? 3 : 1][may1 ? CH : 1];
+  Cx<T> s0v[NBUF][may0 ? 3 : 1][may0 ? CH : 1], s1v[NBUF][may1 ? 3 : 1][may1 ? CH : 1];
   auto load_ops = [&](int c0) {
+    const int buf = (c0 / CH) % NBUF;
 #pragma unroll
     for (int j = 0; j < CH; ++j) {
-      if (c0 + j >= EPT) break;  // an odd register count: the second chunk is one short
+      if (c0 + j >= EPT) break;  // the last chunk may be short
       const int p = F::out_at(t, c0 + j);
       const bool ok = line_kept && F::out_ok(t, c0 + j) && keep(kval(p, N));
       if constexpr (may0) {
         const uint32_t ii0 = (uint32_t)((p * N + yi) * a.li0.pitch + kz);
         if (need0) {
 #pragma unroll
-          for (int c = 0; c < 3; ++c) s0v[c][j] = ld_masked(a.in0 + c * a.li0.cs, ii0, ok);
+          for (int c = 0; c < 3; ++c) s0v[buf][c][j] = ld_masked(a.in0 + c * a.li0.cs, ii0, ok);
         }
       }
       if constexpr (may1) {
         const uint32_t ii1 = (uint32_t)((p * N + yi) * a.li1.pitch + kz);
         if (need1) {
 #pragma unroll
-          for (int c = 0; c < 3; ++c) s1v[c][j] = ld_masked(a.in1 + c * a.li1.cs, ii1, ok);
+          for (int c = 0; c < 3; ++c) s1v[buf][c][j] = ld_masked(a.in1 + c * a.li1.cs, ii1, ok);
         }
       }
     }
@@ -651,9 +669,10 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
   if (FEED == 0 && !epi_on) return;
   const T inv_n3 = T(1) / (T(N) * T(N) * T(N));
   if (epi_on) {
+  if (!active) load_ops(0);
 #pragma unroll
   for (int c0 = 0; c0 < EPT; c0 += CH) {
-  if (c0 > 0 || !active) load_ops(c0);
+  if (c0 + CH < EPT) load_ops(c0 + CH);
 #pragma unroll
   for (int j = 0; j < CH; ++j) {
     const int i = c0 + j;
@@ -701,8 +720,8 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
         O = a.force[c * 196 + ((kx + 3) * 7 + (ky + 3)) * 4 + kz];
       if (op != OP_HEUN1) Nv = Nv + O;  // RK4 slopes N + O (zero for the other ops)
       Cx<T> s0 = cx(T(0), T(0)), s1 = cx(T(0), T(0));
-      if constexpr (may0) s0 = s0v[c][j];
-      if constexpr (may1) s1 = s1v[c][j];
+      if constexpr (may0) s0 = s0v[(c0 / CH) % NBUF][c][j];
+      if constexpr (may1) s1 = s1v[(c0 / CH) % NBUF][c][j];
       Cx<T> v0 = cx(T(0), T(0)), v1 = cx(T(0), T(0));
       if (op == OP_STORE) {
         v0 = Nv;
@@ -755,7 +774,7 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
   if constexpr (FEED != 0) {
     // the next evaluation's x-inverse pass on this tile (as f_xinv<C, CURL>, from registers)
     const bool col = kz < g.kzn;
-    Cx<T> ux[EPT], uy[EPT], uz[EPT], dy[EPT], dz[EPT];
+    Cx<T> ux[EPT], uy[EPT], uz[EPT], v[EPT];
     [[maybe_unused]] const T kyf = T(ky), kzf = T(kz);
     const Cx<T> phyz2 = sh2.on ? phc2[l] : cx(T(1), T(0));
 #pragma unroll
@@ -770,9 +789,6 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
         uy[i] = cmul(uy[i], phi);
         uz[i] = cmul(uz[i], phi);
       }
-      const T kxf = T(kval(p, N));
-      dy[i] = mul_i(scale(uy[i], kxf));
-      dz[i] = mul_i(scale(uz[i], kxf));
     }
     const uint32_t obase = (uint32_t)(yi * g.kzp + kz0) + l, ostep = (uint32_t)(N * g.kzp);
     auto store = [&](int f, const Cx<T>* v) {
@@ -783,6 +799,24 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
             st_off<stream_stores<T>(N)>(W + f * g.wcomp, (uint32_t)FI::out_pos(t, i) * ostep + obase, v[i]);
       }
     };
+    FI::run(ux, t, lv, tw);
+    store(0, ux);
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) v[i] = mul_i(scale(uz[i], T(kval(FI::in_at(t, i), N))));
+    FI::run(v, t, lv, tw);  // D_z
+    if constexpr (CURL) {
+#pragma unroll
+      for (int i = 0; i < EPT; ++i) v[i] = mul_i(scale(ux[i], kzf)) - v[i];  // omega_y
+    }
+    store(4, v);
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) v[i] = mul_i(scale(uy[i], T(kval(FI::in_at(t, i), N))));
+    FI::run(v, t, lv, tw);  // D_y
+    if constexpr (CURL) {
+#pragma unroll
+      for (int i = 0; i < EPT; ++i) v[i] = v[i] - mul_i(scale(ux[i], kyf));  // omega_z
+    }
+    store(5, v);
     FI::run(uy, t, lv, tw);
     store(1, uy);
     FI::run(uz, t, lv, tw);
@@ -792,20 +826,6 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
       for (int i = 0; i < EPT; ++i) uy[i] = mul_i(scale(uz[i], kyf) - scale(uy[i], kzf));  // omega_x
       store(3, uy);
     }
-    FI::run(ux, t, lv, tw);
-    store(0, ux);
-    FI::run(dz, t, lv, tw);
-    if constexpr (CURL) {
-#pragma unroll
-      for (int i = 0; i < EPT; ++i) dz[i] = mul_i(scale(ux[i], kzf)) - dz[i];  // omega_y
-    }
-    store(4, dz);
-    FI::run(dy, t, lv, tw);
-    if constexpr (CURL) {
-#pragma unroll
-      for (int i = 0; i < EPT; ++i) dy[i] = dy[i] - mul_i(scale(ux[i], kyf));  // omega_z
-    }
-    store(5, dy);
   }
 }
 
@@ -820,8 +840,8 @@ using LP64 = LinePlan<64, 8, Radices<8, 8>, Radices<8, 8>>;
 using LP128b = LinePlan<128, 16, Radices<8, 4, 4>, Radices<4, 4, 8>>;
 using LP192 = LinePlan<192, 16, Radices<12, 4, 4>, Radices<4, 4, 12>>;
 using LP256b = LinePlan<256, 32, Radices<8, 8, 4>, Radices<4, 8, 8>>;
-using Fast64 = FastCfg<LP64, LP64, LP64, 16, LP64>;
-using Fast128 = FastCfg<LP128b, LP128b, LP128b, 8, LP128b, LP128b, 8, true>;
+using Fast64 = FastCfg<LP64, LP64, LP64, 16, XPass<LP64, 2>>;
+using Fast128 = FastCfg<LP128b, LP128b, LP128b, 8, XPass<LP128b, 2>, LP128b, 8, true>;
 // z pass of 192: 6 8 4 over 32 threads, 8 registers a transform (the adjoint z
 // pass keeps 12 4 4 over 16)
 using LP192z = LinePlan<192, 32, Radices<6, 8, 4>, Radices<4, 8, 6>>;
@@ -846,7 +866,7 @@ using LP324za = LinePlan<324, 32, Radices<12, 3, 3, 3>, Radices<3, 3, 3, 12>>;
 // tiles of 8 waves, 156-161 registers a thread) rather than on 18 and 24 threads a
 // line (5 and 6 waves a tile, one tile per CU): fused x pass 152 -> 132 us at 216^3,
 // 154 -> 146 us at 240^3
-using Fast216 = FastCfg<LP216z, LP216, LP216z, 4, LP216z>;
+using Fast216 = FastCfg<LP216z, LP216, LP216z, 4, XPass<LP216z, 3>>;
 using Fast324 = FastCfg<LP324, LP324, LP324z, 4, LP324, LP324za, 4>;
 // 384 = 12 4 4 2 (inverse), 32 threads per line, four lines per z block
 using LP384 = LinePlan<384, 32, Radices<12, 4, 4, 2>, Radices<2, 4, 4, 12>>;
@@ -862,7 +882,7 @@ using Fast384 = FastCfg<LP384, LP384, LP384z, 4, LP384, LP384, 4>;
 // line and more registers measured faster than 1024-thread tiles of 128)
 using LP512 = LinePlan<512, 64, Radices<8, 8, 8>, Radices<8, 8, 8>>;
 using LP512x = LinePlan<512, 32, Radices<16, 8, 4>, Radices<4, 8, 16>>;
-using Fast512 = FastCfg<LP512x, LP512, LP512, 4, LP512x>;
+using Fast512 = FastCfg<LP512x, LP512, LP512, 4, XPass<LP512x, 4>>;
 // Grids whose radices do not all divide one points-per-thread count: 12 registers
 // a thread, some butterflies of a stage predicated off (fft_reg.hpp).  144 = 12 12
 // (uniform, 12 threads), 160 = 10 4 4 (16), 240 = 10 4 6 (24), 270 = 9 6 5 (30),
@@ -886,10 +906,10 @@ using LP240z = LinePlan<240, 32, Radices<8, 6, 5>, Radices<5, 6, 8>>;
 using LP270z = LinePlan<270, 32, Radices<10, 3, 9>, Radices<9, 3, 10>>;
 using LP360z = LinePlan<360, 32, Radices<12, 6, 5>, Radices<5, 6, 12>>;
 using LP360za = LinePlan<360, 64, Radices<10, 6, 6>, Radices<6, 6, 10>>;
-using Fast144 = FastCfg<LP144, LP144, LP144z, 8, LP144, LP144z, 8, true>;
+using Fast144 = FastCfg<LP144, LP144, LP144z, 8, XPass<LP144, 3>, LP144z, 8, true>;
 using LP160z = LinePlan<160, 32, Radices<4, 8, 5>, Radices<5, 8, 4>>;
 using Fast160 = FastCfg<LP160, LP160, LP160z, 8, LP160, LP160, 8>;
-using Fast240 = FastCfg<LP240z, LP240, LP240z, 4, LP240z>;
+using Fast240 = FastCfg<LP240z, LP240, LP240z, 4, XPass<LP240z, 3>>;
 using Fast270 = FastCfg<LP270, LP270, LP270z, 4, LP270, LP270z, 4, true>;
 using Fast360 = FastCfg<LP360x, LP360, LP360z, 4, LP360x, LP360za, 4>;
 

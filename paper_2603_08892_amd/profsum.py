@@ -104,7 +104,7 @@ def source_hash():
 
 def classify(name):
     """(grid size or None, pass name) of a kernel name as rocprofv3 prints it."""
-    m = re.match(r"(?:void )?ns::(\w+)<ns::LinePlanD?<(\d+),", name)
+    m = re.match(r"(?:void )?ns::(\w+)<(?:ns::XPass<)?ns::LinePlanD?<(\d+),", name)
     if m:
         kern, n = m.group(1), int(m.group(2))
         if kern == "f_xinv":
@@ -116,7 +116,7 @@ def classify(name):
         if kern == "f_zcross":
             return n, "z_fused"
         if kern == "f_xfwd":
-            feed = re.search(r"> >, -?\d+, (\d+)(?:, (?:true|false))?>\(", name)
+            feed = re.search(r", -?\d+, (\d+)(?:, (?:true|false))?>\(", name)
             return n, "x_forward_inverse" if feed and feed.group(1) != "0" else "x_forward_epilogue"
         return n, {"f_xlam": "lam_x", "f_zadj": "z_adjoint", "f_xadj": "x_adjoint"}.get(kern, kern)
     m = re.match(r"(?:void )?ns::(k_\w+)<", name) or re.match(r"(?:void )?ns::(k_\w+)\(", name)
