@@ -308,8 +308,8 @@ __device__ __forceinline__ void forcing_mode(int i, int* kx, int* ky, int* kz) {
 // and the FP64 record fs.
 template <typename R>
 __global__ void __launch_bounds__(192)
-k_forcing(const Cx<R>* __restrict__ u, Cx<R>* __restrict__ force, ForceState* __restrict__ fs, int n,
-          int pitch, long long comp, uint64_t seed, long long step, double dt, double inj) {
+k_forcing(const Cx<R>* __restrict__ u, Lay lu, Cx<R>* __restrict__ force, ForceState* __restrict__ fs, int n,
+          uint64_t seed, long long step, double dt, double inj) {
   __shared__ double gre[48][3], gim[48][3], pb[48], pg[48];
   __shared__ double amp;
   const int q = threadIdx.x;
@@ -340,18 +340,18 @@ k_forcing(const Cx<R>* __restrict__ u, Cx<R>* __restrict__ force, ForceState* __
     vr[0] -= kx * dr; vr[1] -= ky * dr; vr[2] -= kz * dr;
     vi[0] -= kx * di; vi[1] -= ky * di; vi[2] -= kz * di;
     // B and G contributions of the stored half-spectrum entries of this mode
-    const long long idx = ((long long)((kx + n) % n) * n + (ky + n) % n) * pitch + kz;
+    const long long idx = lay_at(lu, (kx + n) % n, (ky + n) % n, kz, n);
     double b = 0, g2 = 0;
     const double w = (kz == 0) ? 1.0 : 2.0;
     for (int c = 0; c < 3; ++c) {
-      const Cx<R> a = u[c * comp + idx];
+      const Cx<R> a = u[c * lu.cs + idx];
       b += w * ((double)a.re * vr[c] + (double)a.im * vi[c]);
       g2 += w * (vr[c] * vr[c] + vi[c] * vi[c]);
     }
     if (kz == 0) {  // the partner -k holds conj(g)
-      const long long idp = ((long long)((-kx + n) % n) * n + (-ky + n) % n) * pitch;
+      const long long idp = lay_at(lu, (-kx + n) % n, (-ky + n) % n, 0, n);
       for (int c = 0; c < 3; ++c) {
-        const Cx<R> a = u[c * comp + idp];
+        const Cx<R> a = u[c * lu.cs + idp];
         b += (double)a.re * vr[c] - (double)a.im * vi[c];
         g2 += vr[c] * vr[c] + vi[c] * vi[c];
       }

@@ -134,8 +134,8 @@ struct TypedPlan {
   static constexpr int TPL = TPL_;
   static constexpr int L = tile_cols<T>();
   static constexpr int LP = L + 1;
-  // (k_z pitch of a scratch field: at most N/2 rounded up to the tile)
-  static_assert((unsigned long long)sizeof(Cx<T>) * N * N * ((N / 2 + L) / L * L) <= (1ull << 31),
+  // (k_z pitch of a scratch field: at most N/2 rounded up to the tile; one tile of padding a plane)
+  static_assert((unsigned long long)sizeof(Cx<T>) * N * (N * ((N / 2 + L) / L * L) + L) <= (1ull << 31),
                 "32-bit byte offsets and buffer descriptors need fields of at most 2 GiB");
   static constexpr int EPT = Inv_::template ept<N_, TPL_>();
   // z passes (f_zcross): whether the twiddles stay in registers, and how many slices ahead
@@ -236,7 +236,7 @@ f_xinv(const Cx<typename C::T>* __restrict__ S, Lay ls, Cx<typename C::T>* __res
     phyz = phc[l];
   }
   const LineView<T, C::LP> lv{xb + l};
-  const uint32_t sbase = (uint32_t)(yi * ls.pitch + kz0) + l, sstep = (uint32_t)(N * ls.pitch);
+  const uint32_t sbase = (uint32_t)(yi * ls.pitch + kz0) + l, sstep = (uint32_t)(N * ls.pitch + ls.pad);
   [[maybe_unused]] const T kyf = T(ky), kzf = T(kz);
   Cx<T> ux[EPT], uy[EPT], uz[EPT], v[EPT];
   {
@@ -266,7 +266,7 @@ f_xinv(const Cx<typename C::T>* __restrict__ S, Lay ls, Cx<typename C::T>* __res
       uz[i] = cmul(uz[i], phi);
     }
   }
-  const uint32_t obase = (uint32_t)(yi * g.kzp + kz0) + l, ostep = (uint32_t)(N * g.kzp);
+  const uint32_t obase = (uint32_t)(yi * g.kzp + kz0) + l, ostep = (uint32_t)(N * g.kzp + g.pad);
   auto store = [&](int f, const Cx<T>* v) {
     if (col) {
 #pragma unroll
@@ -323,7 +323,7 @@ f_ypass(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__
   for (int i = tid; i < N; i += C::L * TPL) tw[i] = twg[i];
   const bool col = kz < g.kzn;
   Cx<T>* base = W + f * g.wcomp;
-  const uint32_t rbase = (uint32_t)(x * N * g.kzp + kz0) + l;
+  const uint32_t rbase = (uint32_t)(x * (N * g.kzp + g.pad) + kz0) + l;
   const LineView<T, C::LP> lv{xb + l};
   Cx<T> v[EPT];
 #pragma unroll
@@ -376,7 +376,7 @@ f_ycurl(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__
   Cx<T>* const Wa = W + (grp ? 0 : 1) * g.wcomp;
   Cx<T>* const Wb = W + (grp ? 4 : 2) * g.wcomp;
   Cx<T>* const Wc = W + (grp ? 5 : 3) * g.wcomp;
-  const uint32_t rbase = (uint32_t)(x * N * g.kzp + kz0) + l;
+  const uint32_t rbase = (uint32_t)(x * (N * g.kzp + g.pad) + kz0) + l;
   const LineView<T, C::LP> lv{xb + l};
   Cx<T> va[EPT], vb[EPT], vc[EPT];
   {
@@ -460,7 +460,7 @@ f_zcross(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict_
   const int p = tid / TPL, t = tid % TPL;
   const uint32_t line = (uint32_t)blockIdx.x * P + p;
   const LineView<T, 1> lv{xb + p * LP};
-  const uint32_t lbase = line * (uint32_t)g.kzp;
+  const uint32_t lbase = line * (uint32_t)g.kzp + (line / N) * (uint32_t)g.pad;
   const uint32_t fbytes = (uint32_t)(g.wcomp * (long long)sizeof(Cx<T>));
   T fx[EPT], fy[EPT], fz[EPT];
   Cx<T> z[2][EPT];
@@ -620,14 +620,14 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
       const int p = F::out_at(t, c0 + j);
       const bool ok = line_kept && F::out_ok(t, c0 + j) && keep(kval(p, N));
       if constexpr (may0) {
-        const uint32_t ii0 = (uint32_t)((p * N + yi) * a.li0.pitch + kz);
+        const uint32_t ii0 = (uint32_t)((p * N + yi) * a.li0.pitch + p * a.li0.pad + kz);
         if (need0) {
 #pragma unroll
           for (int c = 0; c < 3; ++c) s0v[buf][c][j] = ld_masked(a.in0 + c * a.li0.cs, ii0, ok);
         }
       }
       if constexpr (may1) {
-        const uint32_t ii1 = (uint32_t)((p * N + yi) * a.li1.pitch + kz);
+        const uint32_t ii1 = (uint32_t)((p * N + yi) * a.li1.pitch + p * a.li1.pad + kz);
         if (need1) {
 #pragma unroll
           for (int c = 0; c < 3; ++c) s1v[buf][c][j] = ld_masked(a.in1 + c * a.li1.cs, ii1, ok);
@@ -648,7 +648,7 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
       }
     }
     const bool col = kz < g.kzn;
-    const uint32_t wbase = (uint32_t)(yi * g.kzp + kz0) + l, wstep = (uint32_t)(N * g.kzp);
+    const uint32_t wbase = (uint32_t)(yi * g.kzp + kz0) + l, wstep = (uint32_t)(N * g.kzp + g.pad);
     // field f + 1 is loaded while field f is transformed
 #pragma unroll
     for (int i = 0; i < EPT; ++i) r[0][i] = ld_masked(W, (uint32_t)F::in_at(t, i) * wstep + wbase, col && F::in_ok(t, i));
@@ -680,7 +680,7 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
     if (!F::out_ok(t, i)) continue;  // no point in this register
     const int p = F::out_pos(t, i);
     const int kx = kval(p, N);
-    const uint32_t io0 = (uint32_t)((p * N + yi) * a.lo0.pitch + kz);
+    const uint32_t io0 = (uint32_t)((p * N + yi) * a.lo0.pitch + p * a.lo0.pad + kz);
     if (!(line_kept && keep(kx))) {
       // outside the retained set: zero in outputs that must be complete (full
       // mode, the caller's arrays); stage buffers are only read at retained modes
@@ -688,7 +688,7 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
         for (int c = 0; c < 3; ++c) st_off(a.out0 + c * a.lo0.cs, io0, cx(T(0), T(0)));
       continue;
     }
-    const uint32_t io1 = use1 ? (uint32_t)((p * N + yi) * a.lo1.pitch + kz) : 0u;
+    const uint32_t io1 = use1 ? (uint32_t)((p * N + yi) * a.lo1.pitch + p * a.lo1.pad + kz) : 0u;
     Cx<T> Fv[3] = {scale(r[0][i], inv_n3), scale(r[1][i], inv_n3), scale(r[2][i], inv_n3)};
     if (sh.on) {
       const Cx<T> phi = cmul(phx[p], phyz);
@@ -790,7 +790,7 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
         uz[i] = cmul(uz[i], phi);
       }
     }
-    const uint32_t obase = (uint32_t)(yi * g.kzp + kz0) + l, ostep = (uint32_t)(N * g.kzp);
+    const uint32_t obase = (uint32_t)(yi * g.kzp + kz0) + l, ostep = (uint32_t)(N * g.kzp + g.pad);
     auto store = [&](int f, const Cx<T>* v) {
       if (col) {
 #pragma unroll

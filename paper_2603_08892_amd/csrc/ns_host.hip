@@ -159,7 +159,15 @@ bool make_layout(const ns_config* c, Layout* lay) {
   lay->tx = tx;
   g.kzp = (g.kzn + L - 1) / L * L;
   g.comp = (long long)n * n * g.h;
-  g.wcomp = (long long)n * n * g.kzp;
+  // The x passes walk the x planes: n kzp elements apart, for most sizes a multiple of a
+  // large power of two bytes.  One more 128-byte row a plane spreads the memory channels:
+  // PS-RK2 random steps 971 -> 928 us at 256^3 (every strided pass faster; two rows only half
+  // as much), 758 -> 753 at 240^3, 2.95 -> 2.93 ms at 360^3, RK4 10.42 -> 10.30 ms at 512^3.  On
+  // the grids whose step lives in the last-level cache (those without streaming stores)
+  // it cost up to 2% (128^3 125.1 -> 128.1 us), so they have none.
+  const bool beyond_cache = c->precision == NS_FP32 ? ns::stream_stores<float>(n) : ns::stream_stores<double>(n);
+  g.pad = fast_size(c) && beyond_cache ? L : 0;
+  g.wcomp = (long long)n * (n * g.kzp + g.pad);
   lay->ntz = (g.kzn + L - 1) / L;
   lay->ntzf = (g.h + L - 1) / L;
   // z pass: P lines per block, P a power of two dividing n^2, 3 P n <= kEptZ * tz
@@ -341,8 +349,8 @@ ns_status etab(ns_ctx* c, double dt) {
 template <typename R>
 ns_status forcing_draw(ns_ctx* c, const Cx<R>* x, ns::Lay lx, const ns_forcing* fo, long long step, double dt) {
   Ptrs<R> p = ptrs<R>(c);
-  hipLaunchKernelGGL(ns::k_forcing<R>, dim3(1), dim3(192), 0, c->stream, x, p.force, p.fstate, c->lay.g.n, lx.pitch,
-                     lx.cs, fo->seed, step, dt, fo->injection);
+  hipLaunchKernelGGL(ns::k_forcing<R>, dim3(1), dim3(192), 0, c->stream, x, lx, p.force, p.fstate, c->lay.g.n,
+                     fo->seed, step, dt, fo->injection);
   return hip_check(c, hipGetLastError(), "k_forcing launch");
 }
 

@@ -186,8 +186,8 @@ Ptrs<R> ptrs(ns_ctx* c) {
 inline size_t lds_strided(const Layout& l) { return (size_t)(2 * l.g.n + l.g.n * l.g.L) * l.elem; }
 
 // Layouts: the caller's arrays and the compact internal stage buffers.
-inline ns::Lay user_lay(const Layout& l) { return ns::Lay{l.g.h, l.g.comp}; }
-inline ns::Lay compact_lay(const Layout& l) { return ns::Lay{l.g.kzp, l.g.wcomp}; }
+inline ns::Lay user_lay(const Layout& l) { return ns::Lay{l.g.h, 0, l.g.comp}; }
+inline ns::Lay compact_lay(const Layout& l) { return ns::Lay{l.g.kzp, l.g.pad, l.g.wcomp}; }
 inline ns::Shift make_shift(const double* s) {
   ns::Shift sh;
   sh.s[0] = s ? s[0] : 0.0;

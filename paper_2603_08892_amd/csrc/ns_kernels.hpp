@@ -10,7 +10,8 @@
 //   k_ypass  scratch in place: forward FFT along y (3 fields)
 //   k_xfwd   scratch -> state: forward FFT along x, 1/N^3, deshift, projection,
 //            truncation mask, and the Runge-Kutta stage combination
-// Scratch layout: field f, [x or k_x][y or k_y][k_z < kzn], k_z stride kzp.
+// Scratch layout: field f, [x or k_x][y or k_y][k_z < kzn], k_z stride kzp (the
+// specialised passes pad the x planes, Geom::pad; these kernels run with pad = 0).
 // Only the k_z planes and (k_y, k_z) lines that can hold retained modes are
 // transformed; everything else is known to be zero and is neither read nor
 // written (a pruned transform: the truncation sphere or cube bounds the support).
@@ -24,13 +25,14 @@ struct Geom {
   int n, h;         // N, N/2 + 1
   int kzn;          // k_z planes that can hold retained modes (k_z < kzn)
   int kzp;          // k_z stride of the scratch fields (kzn rounded up)
+  int pad;          // elements between the x planes of a scratch field
   int L;            // k_z columns per strided tile (power of two)
   int lgL;          // log2(L)
   int mask;         // 0 sphere, 1 cube, 2 sphere / 3 cube without the double-alias reach
   int kmax;         // largest retained |k_i|
   long long k2max;  // sphere: largest retained |k|^2; cube: 3 kmax^2
   long long comp;   // state component stride, n*n*h
-  long long wcomp;  // scratch field stride, n*n*kzp
+  long long wcomp;  // scratch field stride, n*(n*kzp + pad)
 };
 
 __device__ __forceinline__ int kval(int i, int n) { return i < (n + 1) / 2 ? i : i - n; }
@@ -78,13 +80,14 @@ __device__ __forceinline__ Cx<R> mul_i(Cx<R> a) { return cx(-a.im, a.re); }
 
 // Addressing of a state-shaped array: the caller's layout [3][N][N][N/2+1]
 // (pitch N/2+1) or the compact internal one [3][N][N][kzp] (k_z < kzn only,
-// rows aligned to the tile width).
+// rows aligned to the tile width, x planes padded as those of the scratch fields).
 struct Lay {
   int pitch;        // k_z pitch of a (k_x, k_y) row
+  int pad;          // elements between the x planes
   long long cs;     // component stride
 };
 __device__ __forceinline__ long long lay_at(const Lay& L, int xi, int yi, int kz, int n) {
-  return ((long long)xi * n + yi) * L.pitch + kz;
+  return ((long long)xi * n + yi) * L.pitch + (long long)xi * L.pad + kz;
 }
 
 // Grid shift s (grid-spacing units); on == 0: unshifted.
