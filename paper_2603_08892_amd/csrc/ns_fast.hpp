@@ -170,7 +170,7 @@ struct LinePlanD : TypedPlan<double, N, TPL, Inv, Fwd> {};
 // An x plan whose one-operand stages take chunks of ONE points (TypedPlan::CHUNK_ONE).
 // PS-RK2 random steps, a quarter of the points against all: 216^3 590 against 625 us, 240^3
 // 758 against 800, 512^3 7.80 against 8.18 ms (fewer registers: two tiles a CU, no spills);
-// 144^3 164 against 165; at 256, 324, 360 and 384 1-2% slower, so those keep all.
+// at 256 and 384 1-2% slower, so those keep all.
 template <typename P, int ONE>
 struct XPass : P {
   static constexpr int CHUNK_ONE = ONE;
@@ -190,6 +190,8 @@ struct FastCfg {
   static constexpr int PZ = PZ_;
   static constexpr int PZA = PZA_;
   static_assert(N * N % PZ_ == 0 && N * N % PZA_ == 0, "the z passes run N^2 / P blocks of P whole lines");
+  // f_xfwd runs the x-inverse pass of a chained evaluation, f_xinv that of a first one
+  static_assert(std::is_base_of_v<XI, XF>, "chained and single evaluations agree bit for bit");
   using XInv = XI;
   using Y = YP;
   using Z = ZP;
@@ -840,19 +842,33 @@ using LP64 = LinePlan<64, 8, Radices<8, 8>, Radices<8, 8>>;
 using LP128b = LinePlan<128, 16, Radices<8, 4, 4>, Radices<4, 4, 8>>;
 using LP192 = LinePlan<192, 16, Radices<12, 4, 4>, Radices<4, 4, 12>>;
 using LP256b = LinePlan<256, 32, Radices<8, 8, 4>, Radices<4, 8, 8>>;
-using Fast64 = FastCfg<LP64, LP64, LP64, 16, XPass<LP64, 2>>;
-using Fast128 = FastCfg<LP128b, LP128b, LP128b, 8, XPass<LP128b, 2>, LP128b, 8, true>;
-// z pass of 192: 6 8 4 over 32 threads, 8 registers a transform (the adjoint z
-// pass keeps 12 4 4 over 16)
+// x plans of 64 to 192, 324, 360 and 384: an x pass waits for its rows, so lines of
+// more threads (16 to 60) with 4 to 10 registers a transform beat fewer threads with more,
+// even where a 16-column tile is then 15 waves and the only one on its CU.  Fused x passes
+// of PS-RK2 random steps, us: 64^3 8 8 over 8 threads 17.6, 4 4 4 over 16 15.6; 128^3 8 4
+// 4 over 16 24.5, 4 8 4 over 32 22.8; 144^3 12 12 over 12 27.1, 6 6 4 over 24 25.9; 160^3
+// 10 4 4 over 16 34.0, 5 8 4 over 32 29.4; 192^3 12 4 4 over 16 65, 6 8 4 over 32 63 (RK4
+// 34.4, 31.7); 324^3 12 3 3 3 over 27 343, 6 6
+// 9 over 54 308; 360^3 12 6 5 over 30 469, 6 10 6 over 60 443; 384^3 12 4 4 2 over 32
+// 507, 8 6 8 over 48 456.  216, 240, 256 and 512 had no better plan (256^3 4 4 4 4 over 64:
+// 163 against 165, but 91 against 86 in RK4).  270 keeps 9 6 5 over 30 threads: 5 6 9 over 54
+// made the fused pass 154 -> 140, but f_xinv 74 -> 85 and the last stage 121 -> 126.  f_xinv and f_xfwd
+// run one plan, so that chained and single evaluations agree bit for bit.
+using LP64x = LinePlan<64, 16, Radices<4, 4, 4>, Radices<4, 4, 4>>;
+using Fast64 = FastCfg<LP64x, LP64, LP64, 16, XPass<LP64x, 2>>;
+using LP128x = LinePlan<128, 32, Radices<4, 8, 4>, Radices<4, 8, 4>>;
+using Fast128 = FastCfg<LP128x, LP128b, LP128b, 8, XPass<LP128x, 2>, LP128b, 8, true>;
+// z and x passes of 192: 6 8 4 over 32 threads, 8 registers a transform (the adjoint z
+// pass and the y passes keep 12 4 4 over 16)
 using LP192z = LinePlan<192, 32, Radices<6, 8, 4>, Radices<4, 8, 6>>;
-using Fast192 = FastCfg<LP192, LP192, LP192z, 8, LP192, LP192, 8>;
+using Fast192 = FastCfg<LP192z, LP192, LP192z, 8, XPass<LP192z, 3>, LP192, 8>;
 // z pass of 256: 4 4 4 4 over 64 threads (4 registers a transform, six waves per
 // SIMD; 5% faster than 8 8 4 over 32 at 256^3, whose extra exchange costs more at
 // 128^3); the adjoint z pass keeps 8 8 4 over 32
 using LP256z = LinePlan<256, 64, Radices<4, 4, 4, 4>, Radices<4, 4, 4, 4>>;
 using Fast256 = FastCfg<LP256b, LP256b, LP256z, 4, LP256b, LP256b, 8, true>;
 // 216 = 12 6 3 and 324 = 12 3 3 3 with 12 points per thread (18 and 27 threads per
-// line): the grids of the k_max = 108 comparison
+// line), the y passes: the grids of the k_max = 108 comparison
 using LP216 = LinePlan<216, 18, Radices<12, 6, 3>, Radices<3, 6, 12>>;
 using LP324 = LinePlan<324, 27, Radices<12, 3, 3, 3>, Radices<3, 3, 3, 12>>;
 // z passes with the line inside one wavefront (wavefront-scope synchronisation
@@ -867,13 +883,15 @@ using LP324za = LinePlan<324, 32, Radices<12, 3, 3, 3>, Radices<3, 3, 3, 12>>;
 // line (5 and 6 waves a tile, one tile per CU): fused x pass 152 -> 132 us at 216^3,
 // 154 -> 146 us at 240^3
 using Fast216 = FastCfg<LP216z, LP216, LP216z, 4, XPass<LP216z, 3>>;
-using Fast324 = FastCfg<LP324, LP324, LP324z, 4, LP324, LP324za, 4>;
-// 384 = 12 4 4 2 (inverse), 32 threads per line, four lines per z block
+using LP324x = LinePlan<324, 54, Radices<6, 6, 9>, Radices<9, 6, 6>>;
+using Fast324 = FastCfg<LP324x, LP324, LP324z, 4, XPass<LP324x, 3>, LP324za, 4>;
+// y passes of 384: 12 4 4 2 (inverse), 32 threads per line
 using LP384 = LinePlan<384, 32, Radices<12, 4, 4, 2>, Radices<2, 4, 4, 12>>;
 // z pass of 384: 6 8 8 over 64 threads, 8 registers and two exchanges a transform
 // (the adjoint z pass keeps 12 4 4 2 over 32)
 using LP384z = LinePlan<384, 64, Radices<6, 8, 8>, Radices<8, 8, 6>>;
-using Fast384 = FastCfg<LP384, LP384, LP384z, 4, LP384, LP384, 4>;
+using LP384x = LinePlan<384, 48, Radices<8, 6, 8>, Radices<8, 6, 8>>;
+using Fast384 = FastCfg<LP384x, LP384, LP384z, 4, LP384x, LP384, 4>;
 // 512 (the 2/3-truncated RK4 grid of the 512^3 comparison): y and z passes 8 8 8
 // with one wavefront per line, four lines per z block (at eight, one 512-thread
 // block of about 130 registers a thread is all a CU holds); x passes 16 8 4 with
@@ -886,17 +904,14 @@ using Fast512 = FastCfg<LP512x, LP512, LP512, 4, XPass<LP512x, 4>>;
 // Grids whose radices do not all divide one points-per-thread count: 12 registers
 // a thread, some butterflies of a stage predicated off (fft_reg.hpp).  144 = 12 12
 // (uniform, 12 threads), 160 = 10 4 4 (16), 240 = 10 4 6 (24), 270 = 9 6 5 (30),
-// 360 = 10 6 6 (36, the y pass): the truncation sweeps at k_max = 64 and 108 and the
+// 360 = 10 4 9 (40, the y pass): the truncation sweeps at k_max = 64 and 108 and the
 // coarse grid of the 512^3 comparison at C_t = 0.948.
 using LP144 = LinePlan<144, 12, Radices<12, 12>, Radices<12, 12>>;
 using LP160 = LinePlan<160, 16, Radices<10, 4, 4>, Radices<4, 4, 10>>;
 using LP240 = LinePlan<240, 24, Radices<10, 4, 6>, Radices<6, 4, 10>>;
 using LP270 = LinePlan<270, 30, Radices<9, 6, 5>, Radices<5, 6, 9>>;
-using LP360 = LinePlan<360, 36, Radices<10, 6, 6>, Radices<6, 6, 10>>;
-// x passes of 360: 30 threads per line (12 6 5, up to 15 registers a transform), so
-// that a 16-column tile is a 480-thread block that may hold 256 registers a thread
-// (576 threads allow 168, and the x-forward passes spilled)
-using LP360x = LinePlan<360, 30, Radices<12, 6, 5>, Radices<5, 6, 12>>;
+// y passes of 360: 348 + 157 us on 40 threads a line, 10 6 6 on 36 took 363 + 180
+using LP360 = LinePlan<360, 40, Radices<10, 4, 9>, Radices<9, 4, 10>>;
 // z passes with lines inside one wavefront and few registers a thread: 144 = 6 6 4,
 // 160 = 4 8 5, 240 = 8 6 5, 270 = 10 3 9, 360 = 12 6 5, all over 32 threads (8 to
 // 15 registers a transform); the adjoint z passes of 160 and 360, which hold eight
@@ -906,11 +921,14 @@ using LP240z = LinePlan<240, 32, Radices<8, 6, 5>, Radices<5, 6, 8>>;
 using LP270z = LinePlan<270, 32, Radices<10, 3, 9>, Radices<9, 3, 10>>;
 using LP360z = LinePlan<360, 32, Radices<12, 6, 5>, Radices<5, 6, 12>>;
 using LP360za = LinePlan<360, 64, Radices<10, 6, 6>, Radices<6, 6, 10>>;
-using Fast144 = FastCfg<LP144, LP144, LP144z, 8, XPass<LP144, 3>, LP144z, 8, true>;
+using LP144x = LinePlan<144, 24, Radices<6, 6, 4>, Radices<4, 6, 6>>;
+using Fast144 = FastCfg<LP144x, LP144, LP144z, 8, XPass<LP144x, 3>, LP144z, 8, true>;
 using LP160z = LinePlan<160, 32, Radices<4, 8, 5>, Radices<5, 8, 4>>;
-using Fast160 = FastCfg<LP160, LP160, LP160z, 8, LP160, LP160, 8>;
+using LP160x = LinePlan<160, 32, Radices<5, 8, 4>, Radices<4, 8, 5>>;
+using Fast160 = FastCfg<LP160x, LP160, LP160z, 8, XPass<LP160x, 3>, LP160, 8>;
 using Fast240 = FastCfg<LP240z, LP240, LP240z, 4, XPass<LP240z, 3>>;
 using Fast270 = FastCfg<LP270, LP270, LP270z, 4, LP270, LP270z, 4, true>;
-using Fast360 = FastCfg<LP360x, LP360, LP360z, 4, LP360x, LP360za, 4>;
+using LP360x = LinePlan<360, 60, Radices<6, 10, 6>, Radices<6, 10, 6>>;
+using Fast360 = FastCfg<LP360x, LP360, LP360z, 4, XPass<LP360x, 6>, LP360za, 4>;
 
 }  // namespace ns

@@ -14,12 +14,21 @@
 // 70 + 11.5 EPT (x of FP32), 90 + 24 EPT (x of FP64), 36 + 5 w EPT (y) and 40 + 13 w EPT (z), w = 1 (FP32) or 2 (FP64);
 // up to N = 80, where a launch does not fill the chip, the one with the fewest
 // instructions a thread.  z passes keep a line inside one wavefront (4, 8, 16, 32
-// or 64 threads), and the lines per block divide N^2.
+// or 64 threads), and the lines per block divide N^2.  The x plans were then timed
+// against up to five others, the two cheapest estimates in each of five ranges of threads
+// a line (to 64 threads in FP32, 128 in FP64; EPT at most 12 and 10), PS-RK2 random and
+// RK4 steps and the gradient, and replaced where the steps were 1.5% faster or more: the x
+// passes of FP32 want more threads a line and 5 to 10 registers a transform than the
+// estimate gave (their x-forward kernel holds operands for every stage).  Random steps, us:
+// 100^3 10 10 over 12 to 5 4 5 over 25 131 -> 114, 150^3 3 5 10 over 16 to 6 5 5
+// over 32 approx 285 -> 244, 288^3 2 12 12 over 24 to 6 6 8 over 48 1690 -> 1530, 500^3
+// 5 10 10 over 28 to 10 5 10 over 50 13.4 -> 10.3 ms; FP64 384^3 8 6 8 to 6 8 8 over 64 6.40 ->
+// 6.07 ms.
 //
 // Against the size-generic passes these sizes ran before (LDS Stockham stages over a
 // runtime plan: an LDS round trip and two barriers a radix, index divisions, shift
-// factors evaluated per point): five approx steps at 150^3 FP32 4.71 -> 1.50 ms, two
-// RK4 steps at 128^3 FP64 1.70 -> 0.71 ms, ten exact steps at 32^3 FP64 2.43 -> 1.00 ms.
+// factors evaluated per point): five approx steps at 150^3 FP32 4.71 -> 1.24 ms, two
+// RK4 steps at 128^3 FP64 1.70 -> 0.68 ms, ten exact steps at 32^3 FP64 2.43 -> 1.00 ms.
 #pragma once
 
 #include "ns_fast.hpp"
@@ -36,28 +45,28 @@ template <> struct SizePlan<float, 16> {
   static constexpr int PZ = 32, PZA = 32;
 };
 template <> struct SizePlan<float, 18> {
-  using X = LinePlan<18, 8, Radices<6, 3>, Radices<3, 6>>;
+  using X = LinePlan<18, 6, Radices<6, 3>, Radices<3, 6>>;
   using Y = LinePlan<18, 8, Radices<6, 3>, Radices<3, 6>>;
   using Z = LinePlan<18, 16, Radices<6, 3>, Radices<3, 6>>;
   using ZA = LinePlan<18, 16, Radices<6, 3>, Radices<3, 6>>;
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<float, 20> {
-  using X = LinePlan<20, 8, Radices<5, 4>, Radices<4, 5>>;
+  using X = LinePlan<20, 5, Radices<5, 4>, Radices<4, 5>>;
   using Y = LinePlan<20, 8, Radices<5, 4>, Radices<4, 5>>;
   using Z = LinePlan<20, 8, Radices<5, 4>, Radices<4, 5>>;
   using ZA = LinePlan<20, 8, Radices<5, 4>, Radices<4, 5>>;
   static constexpr int PZ = 16, PZA = 16;
 };
 template <> struct SizePlan<float, 24> {
-  using X = LinePlan<24, 8, Radices<6, 4>, Radices<4, 6>>;
+  using X = LinePlan<24, 16, Radices<4, 2, 3>, Radices<3, 2, 4>>;
   using Y = LinePlan<24, 8, Radices<6, 4>, Radices<4, 6>>;
   using Z = LinePlan<24, 16, Radices<4, 2, 3>, Radices<3, 2, 4>>;
   using ZA = LinePlan<24, 16, Radices<4, 2, 3>, Radices<3, 2, 4>>;
   static constexpr int PZ = 16, PZA = 16;
 };
 template <> struct SizePlan<float, 30> {
-  using X = LinePlan<30, 8, Radices<6, 5>, Radices<5, 6>>;
+  using X = LinePlan<30, 15, Radices<5, 2, 3>, Radices<3, 2, 5>>;
   using Y = LinePlan<30, 8, Radices<6, 5>, Radices<5, 6>>;
   using Z = LinePlan<30, 16, Radices<5, 2, 3>, Radices<3, 2, 5>>;
   using ZA = LinePlan<30, 16, Radices<5, 2, 3>, Radices<3, 2, 5>>;
@@ -71,14 +80,14 @@ template <> struct SizePlan<float, 32> {
   static constexpr int PZ = 16, PZA = 16;
 };
 template <> struct SizePlan<float, 36> {
-  using X = LinePlan<36, 12, Radices<4, 3, 3>, Radices<3, 3, 4>>;
+  using X = LinePlan<36, 12, Radices<3, 3, 4>, Radices<4, 3, 3>>;
   using Y = LinePlan<36, 12, Radices<4, 3, 3>, Radices<3, 3, 4>>;
   using Z = LinePlan<36, 16, Radices<4, 3, 3>, Radices<3, 3, 4>>;
   using ZA = LinePlan<36, 16, Radices<4, 3, 3>, Radices<3, 3, 4>>;
   static constexpr int PZ = 16, PZA = 16;
 };
 template <> struct SizePlan<float, 40> {
-  using X = LinePlan<40, 20, Radices<5, 2, 4>, Radices<4, 2, 5>>;
+  using X = LinePlan<40, 20, Radices<4, 2, 5>, Radices<5, 2, 4>>;
   using Y = LinePlan<40, 20, Radices<5, 2, 4>, Radices<4, 2, 5>>;
   using Z = LinePlan<40, 32, Radices<5, 2, 4>, Radices<4, 2, 5>>;
   using ZA = LinePlan<40, 32, Radices<5, 2, 4>, Radices<4, 2, 5>>;
@@ -99,7 +108,7 @@ template <> struct SizePlan<float, 50> {
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<float, 54> {
-  using X = LinePlan<54, 20, Radices<6, 3, 3>, Radices<3, 3, 6>>;
+  using X = LinePlan<54, 18, Radices<6, 3, 3>, Radices<3, 3, 6>>;
   using Y = LinePlan<54, 20, Radices<6, 3, 3>, Radices<3, 3, 6>>;
   using Z = LinePlan<54, 32, Radices<6, 3, 3>, Radices<3, 3, 6>>;
   using ZA = LinePlan<54, 32, Radices<6, 3, 3>, Radices<3, 3, 6>>;
@@ -113,7 +122,7 @@ template <> struct SizePlan<float, 60> {
   static constexpr int PZ = 8, PZA = 8;
 };
 template <> struct SizePlan<float, 72> {
-  using X = LinePlan<72, 24, Radices<6, 3, 4>, Radices<4, 3, 6>>;
+  using X = LinePlan<72, 36, Radices<4, 2, 3, 3>, Radices<3, 3, 2, 4>>;
   using Y = LinePlan<72, 24, Radices<6, 3, 4>, Radices<4, 3, 6>>;
   using Z = LinePlan<72, 64, Radices<4, 2, 3, 3>, Radices<3, 3, 2, 4>>;
   using ZA = LinePlan<72, 64, Radices<4, 2, 3, 3>, Radices<3, 3, 2, 4>>;
@@ -127,112 +136,112 @@ template <> struct SizePlan<float, 80> {
   static constexpr int PZ = 8, PZA = 8;
 };
 template <> struct SizePlan<float, 90> {
-  using X = LinePlan<90, 12, Radices<10, 9>, Radices<9, 10>>;
+  using X = LinePlan<90, 30, Radices<6, 3, 5>, Radices<5, 3, 6>>;
   using Y = LinePlan<90, 12, Radices<10, 9>, Radices<9, 10>>;
   using Z = LinePlan<90, 16, Radices<10, 9>, Radices<9, 10>>;
   using ZA = LinePlan<90, 16, Radices<10, 9>, Radices<9, 10>>;
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<float, 96> {
-  using X = LinePlan<96, 16, Radices<8, 2, 6>, Radices<6, 2, 8>>;
+  using X = LinePlan<96, 48, Radices<4, 2, 3, 4>, Radices<4, 3, 2, 4>>;
   using Y = LinePlan<96, 12, Radices<12, 8>, Radices<8, 12>>;
   using Z = LinePlan<96, 16, Radices<8, 2, 6>, Radices<6, 2, 8>>;
   using ZA = LinePlan<96, 16, Radices<8, 2, 6>, Radices<6, 2, 8>>;
   static constexpr int PZ = 16, PZA = 16;
 };
 template <> struct SizePlan<float, 100> {
-  using X = LinePlan<100, 12, Radices<10, 10>, Radices<10, 10>>;
+  using X = LinePlan<100, 25, Radices<5, 4, 5>, Radices<5, 4, 5>>;
   using Y = LinePlan<100, 12, Radices<10, 10>, Radices<10, 10>>;
   using Z = LinePlan<100, 16, Radices<10, 10>, Radices<10, 10>>;
   using ZA = LinePlan<100, 16, Radices<10, 10>, Radices<10, 10>>;
   static constexpr int PZ = 16, PZA = 16;
 };
 template <> struct SizePlan<float, 108> {
-  using X = LinePlan<108, 12, Radices<12, 9>, Radices<9, 12>>;
+  using X = LinePlan<108, 32, Radices<3, 6, 6>, Radices<6, 6, 3>>;
   using Y = LinePlan<108, 12, Radices<12, 9>, Radices<9, 12>>;
   using Z = LinePlan<108, 16, Radices<3, 4, 9>, Radices<9, 4, 3>>;
   using ZA = LinePlan<108, 16, Radices<3, 4, 9>, Radices<9, 4, 3>>;
   static constexpr int PZ = 16, PZA = 16;
 };
 template <> struct SizePlan<float, 120> {
-  using X = LinePlan<120, 12, Radices<12, 10>, Radices<10, 12>>;
+  using X = LinePlan<120, 12, Radices<10, 12>, Radices<12, 10>>;
   using Y = LinePlan<120, 12, Radices<12, 10>, Radices<10, 12>>;
   using Z = LinePlan<120, 16, Radices<10, 4, 3>, Radices<3, 4, 10>>;
   using ZA = LinePlan<120, 32, Radices<6, 4, 5>, Radices<5, 4, 6>>;
   static constexpr int PZ = 16, PZA = 8;
 };
 template <> struct SizePlan<float, 150> {
-  using X = LinePlan<150, 16, Radices<3, 5, 10>, Radices<10, 5, 3>>;
+  using X = LinePlan<150, 32, Radices<6, 5, 5>, Radices<5, 5, 6>>;
   using Y = LinePlan<150, 16, Radices<3, 5, 10>, Radices<10, 5, 3>>;
   using Z = LinePlan<150, 32, Radices<6, 5, 5>, Radices<5, 5, 6>>;
   using ZA = LinePlan<150, 32, Radices<6, 5, 5>, Radices<5, 5, 6>>;
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<float, 162> {
-  using X = LinePlan<162, 28, Radices<9, 3, 6>, Radices<6, 3, 9>>;
+  using X = LinePlan<162, 54, Radices<6, 3, 3, 3>, Radices<3, 3, 3, 6>>;
   using Y = LinePlan<162, 20, Radices<2, 9, 9>, Radices<9, 9, 2>>;
   using Z = LinePlan<162, 32, Radices<9, 3, 6>, Radices<6, 3, 9>>;
   using ZA = LinePlan<162, 32, Radices<3, 3, 3, 6>, Radices<6, 3, 3, 3>>;
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<float, 180> {
-  using X = LinePlan<180, 32, Radices<5, 6, 6>, Radices<6, 6, 5>>;
+  using X = LinePlan<180, 36, Radices<6, 5, 6>, Radices<6, 5, 6>>;
   using Y = LinePlan<180, 20, Radices<2, 9, 10>, Radices<10, 9, 2>>;
   using Z = LinePlan<180, 32, Radices<5, 6, 6>, Radices<6, 6, 5>>;
   using ZA = LinePlan<180, 32, Radices<5, 6, 6>, Radices<6, 6, 5>>;
   static constexpr int PZ = 8, PZA = 8;
 };
 template <> struct SizePlan<float, 200> {
-  using X = LinePlan<200, 20, Radices<2, 10, 10>, Radices<10, 10, 2>>;
+  using X = LinePlan<200, 50, Radices<5, 2, 4, 5>, Radices<5, 4, 2, 5>>;
   using Y = LinePlan<200, 20, Radices<2, 10, 10>, Radices<10, 10, 2>>;
   using Z = LinePlan<200, 32, Radices<5, 4, 10>, Radices<10, 4, 5>>;
   using ZA = LinePlan<200, 32, Radices<5, 4, 10>, Radices<10, 4, 5>>;
   static constexpr int PZ = 8, PZA = 8;
 };
 template <> struct SizePlan<float, 250> {
-  using X = LinePlan<250, 28, Radices<5, 5, 10>, Radices<10, 5, 5>>;
+  using X = LinePlan<250, 50, Radices<2, 5, 5, 5>, Radices<5, 5, 5, 2>>;
   using Y = LinePlan<250, 28, Radices<5, 5, 10>, Radices<10, 5, 5>>;
   using Z = LinePlan<250, 32, Radices<5, 5, 10>, Radices<10, 5, 5>>;
   using ZA = LinePlan<250, 32, Radices<5, 5, 10>, Radices<10, 5, 5>>;
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<float, 288> {
-  using X = LinePlan<288, 24, Radices<2, 12, 12>, Radices<12, 12, 2>>;
+  using X = LinePlan<288, 48, Radices<6, 6, 8>, Radices<8, 6, 6>>;
   using Y = LinePlan<288, 24, Radices<2, 12, 12>, Radices<12, 12, 2>>;
   using Z = LinePlan<288, 64, Radices<8, 6, 6>, Radices<6, 6, 8>>;
   using ZA = LinePlan<288, 64, Radices<8, 6, 6>, Radices<6, 6, 8>>;
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<float, 300> {
-  using X = LinePlan<300, 32, Radices<3, 10, 10>, Radices<10, 10, 3>>;
+  using X = LinePlan<300, 60, Radices<2, 5, 5, 6>, Radices<6, 5, 5, 2>>;
   using Y = LinePlan<300, 32, Radices<3, 10, 10>, Radices<10, 10, 3>>;
   using Z = LinePlan<300, 64, Radices<2, 5, 5, 6>, Radices<6, 5, 5, 2>>;
   using ZA = LinePlan<300, 64, Radices<2, 5, 5, 6>, Radices<6, 5, 5, 2>>;
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<float, 320> {
-  using X = LinePlan<320, 32, Radices<4, 2, 10, 4>, Radices<4, 10, 2, 4>>;
+  using X = LinePlan<320, 40, Radices<10, 4, 8>, Radices<8, 4, 10>>;
   using Y = LinePlan<320, 40, Radices<10, 4, 8>, Radices<8, 4, 10>>;
   using Z = LinePlan<320, 64, Radices<8, 5, 8>, Radices<8, 5, 8>>;
   using ZA = LinePlan<320, 64, Radices<8, 5, 8>, Radices<8, 5, 8>>;
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<float, 400> {
-  using X = LinePlan<400, 28, Radices<16, 5, 5>, Radices<5, 5, 16>>;
+  using X = LinePlan<400, 40, Radices<10, 10, 4>, Radices<4, 10, 10>>;
   using Y = LinePlan<400, 40, Radices<4, 10, 10>, Radices<10, 10, 4>>;
   using Z = LinePlan<400, 64, Radices<10, 4, 10>, Radices<10, 4, 10>>;
   using ZA = LinePlan<400, 64, Radices<10, 4, 10>, Radices<10, 4, 10>>;
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<float, 432> {
-  using X = LinePlan<432, 32, Radices<16, 3, 3, 3>, Radices<3, 3, 3, 16>>;
+  using X = LinePlan<432, 54, Radices<3, 4, 4, 9>, Radices<9, 4, 4, 3>>;
   using Y = LinePlan<432, 36, Radices<3, 12, 12>, Radices<12, 12, 3>>;
   using Z = LinePlan<432, 64, Radices<3, 4, 4, 9>, Radices<9, 4, 4, 3>>;
   using ZA = LinePlan<432, 64, Radices<3, 4, 4, 9>, Radices<9, 4, 4, 3>>;
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<float, 450> {
-  using X = LinePlan<450, 32, Radices<6, 3, 5, 5>, Radices<5, 5, 3, 6>>;
+  using X = LinePlan<450, 45, Radices<3, 5, 10, 3>, Radices<3, 10, 5, 3>>;
   using Y = LinePlan<450, 52, Radices<5, 9, 10>, Radices<10, 9, 5>>;
   using Z = LinePlan<450, 64, Radices<5, 9, 10>, Radices<10, 9, 5>>;
   using ZA = LinePlan<450, 64, Radices<5, 9, 10>, Radices<10, 9, 5>>;
@@ -246,49 +255,49 @@ template <> struct SizePlan<float, 480> {
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<float, 486> {
-  using X = LinePlan<486, 28, Radices<6, 9, 9>, Radices<9, 9, 6>>;
+  using X = LinePlan<486, 64, Radices<3, 9, 2, 9>, Radices<9, 2, 9, 3>>;
   using Y = LinePlan<486, 56, Radices<6, 9, 9>, Radices<9, 9, 6>>;
   using Z = LinePlan<486, 64, Radices<3, 2, 9, 9>, Radices<9, 9, 2, 3>>;
   using ZA = LinePlan<486, 64, Radices<3, 2, 9, 9>, Radices<9, 9, 2, 3>>;
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<float, 500> {
-  using X = LinePlan<500, 28, Radices<5, 10, 10>, Radices<10, 10, 5>>;
+  using X = LinePlan<500, 50, Radices<10, 5, 10>, Radices<10, 5, 10>>;
   using Y = LinePlan<500, 52, Radices<5, 10, 10>, Radices<10, 10, 5>>;
   using Z = LinePlan<500, 64, Radices<5, 10, 10>, Radices<10, 10, 5>>;
   using ZA = LinePlan<500, 64, Radices<5, 10, 10>, Radices<10, 10, 5>>;
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<double, 16> {
-  using X = LinePlanD<16, 8, Radices<4, 4>, Radices<4, 4>>;
+  using X = LinePlanD<16, 8, Radices<4, 2, 2>, Radices<2, 2, 4>>;
   using Y = LinePlanD<16, 8, Radices<4, 4>, Radices<4, 4>>;
   using Z = LinePlanD<16, 8, Radices<4, 4>, Radices<4, 4>>;
   using ZA = LinePlanD<16, 8, Radices<4, 4>, Radices<4, 4>>;
   static constexpr int PZ = 32, PZA = 32;
 };
 template <> struct SizePlan<double, 18> {
-  using X = LinePlanD<18, 8, Radices<6, 3>, Radices<3, 6>>;
+  using X = LinePlanD<18, 6, Radices<6, 3>, Radices<3, 6>>;
   using Y = LinePlanD<18, 8, Radices<6, 3>, Radices<3, 6>>;
   using Z = LinePlanD<18, 16, Radices<6, 3>, Radices<3, 6>>;
   using ZA = LinePlanD<18, 16, Radices<6, 3>, Radices<3, 6>>;
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<double, 20> {
-  using X = LinePlanD<20, 8, Radices<5, 4>, Radices<4, 5>>;
+  using X = LinePlanD<20, 8, Radices<4, 5>, Radices<5, 4>>;
   using Y = LinePlanD<20, 8, Radices<5, 4>, Radices<4, 5>>;
   using Z = LinePlanD<20, 8, Radices<5, 4>, Radices<4, 5>>;
   using ZA = LinePlanD<20, 8, Radices<5, 4>, Radices<4, 5>>;
   static constexpr int PZ = 16, PZA = 16;
 };
 template <> struct SizePlan<double, 24> {
-  using X = LinePlanD<24, 8, Radices<6, 4>, Radices<4, 6>>;
+  using X = LinePlanD<24, 12, Radices<4, 2, 3>, Radices<3, 2, 4>>;
   using Y = LinePlanD<24, 8, Radices<6, 4>, Radices<4, 6>>;
   using Z = LinePlanD<24, 8, Radices<6, 4>, Radices<4, 6>>;
   using ZA = LinePlanD<24, 8, Radices<6, 4>, Radices<4, 6>>;
   static constexpr int PZ = 32, PZA = 32;
 };
 template <> struct SizePlan<double, 30> {
-  using X = LinePlanD<30, 8, Radices<6, 5>, Radices<5, 6>>;
+  using X = LinePlanD<30, 15, Radices<5, 2, 3>, Radices<3, 2, 5>>;
   using Y = LinePlanD<30, 8, Radices<6, 5>, Radices<5, 6>>;
   using Z = LinePlanD<30, 16, Radices<5, 2, 3>, Radices<3, 2, 5>>;
   using ZA = LinePlanD<30, 16, Radices<5, 2, 3>, Radices<3, 2, 5>>;
@@ -302,7 +311,7 @@ template <> struct SizePlan<double, 32> {
   static constexpr int PZ = 16, PZA = 16;
 };
 template <> struct SizePlan<double, 36> {
-  using X = LinePlanD<36, 16, Radices<4, 3, 3>, Radices<3, 3, 4>>;
+  using X = LinePlanD<36, 12, Radices<3, 3, 4>, Radices<4, 3, 3>>;
   using Y = LinePlanD<36, 16, Radices<4, 3, 3>, Radices<3, 3, 4>>;
   using Z = LinePlanD<36, 16, Radices<4, 3, 3>, Radices<3, 3, 4>>;
   using ZA = LinePlanD<36, 16, Radices<4, 3, 3>, Radices<3, 3, 4>>;
@@ -323,7 +332,7 @@ template <> struct SizePlan<double, 48> {
   static constexpr int PZ = 16, PZA = 16;
 };
 template <> struct SizePlan<double, 50> {
-  using X = LinePlanD<50, 32, Radices<5, 2, 5>, Radices<5, 2, 5>>;
+  using X = LinePlanD<50, 25, Radices<5, 2, 5>, Radices<5, 2, 5>>;
   using Y = LinePlanD<50, 32, Radices<5, 2, 5>, Radices<5, 2, 5>>;
   using Z = LinePlanD<50, 32, Radices<5, 2, 5>, Radices<5, 2, 5>>;
   using ZA = LinePlanD<50, 32, Radices<5, 2, 5>, Radices<5, 2, 5>>;
@@ -351,7 +360,7 @@ template <> struct SizePlan<double, 64> {
   static constexpr int PZ = 16, PZA = 16;
 };
 template <> struct SizePlan<double, 72> {
-  using X = LinePlanD<72, 24, Radices<6, 3, 4>, Radices<4, 3, 6>>;
+  using X = LinePlanD<72, 36, Radices<4, 2, 3, 3>, Radices<3, 3, 2, 4>>;
   using Y = LinePlanD<72, 24, Radices<6, 3, 4>, Radices<4, 3, 6>>;
   using Z = LinePlanD<72, 32, Radices<6, 3, 4>, Radices<4, 3, 6>>;
   using ZA = LinePlanD<72, 32, Radices<6, 3, 4>, Radices<4, 3, 6>>;
@@ -372,7 +381,7 @@ template <> struct SizePlan<double, 90> {
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<double, 96> {
-  using X = LinePlanD<96, 24, Radices<6, 4, 4>, Radices<4, 4, 6>>;
+  using X = LinePlanD<96, 24, Radices<4, 4, 6>, Radices<6, 4, 4>>;
   using Y = LinePlanD<96, 16, Radices<8, 2, 6>, Radices<6, 2, 8>>;
   using Z = LinePlanD<96, 16, Radices<8, 2, 6>, Radices<6, 2, 8>>;
   using ZA = LinePlanD<96, 16, Radices<8, 2, 6>, Radices<6, 2, 8>>;
@@ -393,7 +402,7 @@ template <> struct SizePlan<double, 108> {
   static constexpr int PZ = 8, PZA = 16;
 };
 template <> struct SizePlan<double, 120> {
-  using X = LinePlanD<120, 32, Radices<6, 4, 5>, Radices<5, 4, 6>>;
+  using X = LinePlanD<120, 30, Radices<5, 4, 6>, Radices<6, 4, 5>>;
   using Y = LinePlanD<120, 32, Radices<6, 4, 5>, Radices<5, 4, 6>>;
   using Z = LinePlanD<120, 32, Radices<6, 4, 5>, Radices<5, 4, 6>>;
   using ZA = LinePlanD<120, 16, Radices<10, 4, 3>, Radices<3, 4, 10>>;
@@ -414,7 +423,7 @@ template <> struct SizePlan<double, 144> {
   static constexpr int PZ = 8, PZA = 4;
 };
 template <> struct SizePlan<double, 150> {
-  using X = LinePlanD<150, 32, Radices<6, 5, 5>, Radices<5, 5, 6>>;
+  using X = LinePlanD<150, 30, Radices<5, 5, 6>, Radices<6, 5, 5>>;
   using Y = LinePlanD<150, 32, Radices<6, 5, 5>, Radices<5, 5, 6>>;
   using Z = LinePlanD<150, 32, Radices<6, 5, 5>, Radices<5, 5, 6>>;
   using ZA = LinePlanD<150, 32, Radices<6, 5, 5>, Radices<5, 5, 6>>;
@@ -428,14 +437,14 @@ template <> struct SizePlan<double, 160> {
   static constexpr int PZ = 8, PZA = 8;
 };
 template <> struct SizePlan<double, 162> {
-  using X = LinePlanD<162, 32, Radices<6, 3, 3, 3>, Radices<3, 3, 3, 6>>;
+  using X = LinePlanD<162, 27, Radices<6, 3, 3, 3>, Radices<3, 3, 3, 6>>;
   using Y = LinePlanD<162, 24, Radices<9, 2, 9>, Radices<9, 2, 9>>;
   using Z = LinePlanD<162, 32, Radices<6, 3, 3, 3>, Radices<3, 3, 3, 6>>;
   using ZA = LinePlanD<162, 32, Radices<9, 3, 6>, Radices<6, 3, 9>>;
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<double, 180> {
-  using X = LinePlanD<180, 40, Radices<6, 5, 6>, Radices<6, 5, 6>>;
+  using X = LinePlanD<180, 36, Radices<6, 6, 5>, Radices<5, 6, 6>>;
   using Y = LinePlanD<180, 40, Radices<6, 5, 6>, Radices<6, 5, 6>>;
   using Z = LinePlanD<180, 64, Radices<5, 3, 3, 4>, Radices<4, 3, 3, 5>>;
   using ZA = LinePlanD<180, 64, Radices<5, 3, 3, 4>, Radices<4, 3, 3, 5>>;
@@ -470,7 +479,7 @@ template <> struct SizePlan<double, 240> {
   static constexpr int PZ = 4, PZA = 8;
 };
 template <> struct SizePlan<double, 250> {
-  using X = LinePlanD<250, 64, Radices<5, 2, 5, 5>, Radices<5, 5, 2, 5>>;
+  using X = LinePlanD<250, 50, Radices<5, 5, 10>, Radices<10, 5, 5>>;
   using Y = LinePlanD<250, 32, Radices<10, 5, 5>, Radices<5, 5, 10>>;
   using Z = LinePlanD<250, 64, Radices<5, 2, 5, 5>, Radices<5, 5, 2, 5>>;
   using ZA = LinePlanD<250, 64, Radices<5, 2, 5, 5>, Radices<5, 5, 2, 5>>;
@@ -491,7 +500,7 @@ template <> struct SizePlan<double, 270> {
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<double, 288> {
-  using X = LinePlanD<288, 48, Radices<8, 6, 6>, Radices<6, 6, 8>>;
+  using X = LinePlanD<288, 48, Radices<6, 6, 8>, Radices<8, 6, 6>>;
   using Y = LinePlanD<288, 40, Radices<9, 4, 8>, Radices<8, 4, 9>>;
   using Z = LinePlanD<288, 64, Radices<8, 6, 6>, Radices<6, 6, 8>>;
   using ZA = LinePlanD<288, 64, Radices<8, 6, 6>, Radices<6, 6, 8>>;
@@ -505,7 +514,7 @@ template <> struct SizePlan<double, 300> {
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<double, 320> {
-  using X = LinePlanD<320, 64, Radices<8, 5, 8>, Radices<8, 5, 8>>;
+  using X = LinePlanD<320, 80, Radices<4, 4, 4, 5>, Radices<5, 4, 4, 4>>;
   using Y = LinePlanD<320, 40, Radices<10, 4, 8>, Radices<8, 4, 10>>;
   using Z = LinePlanD<320, 64, Radices<8, 5, 8>, Radices<8, 5, 8>>;
   using ZA = LinePlanD<320, 64, Radices<8, 5, 8>, Radices<8, 5, 8>>;
@@ -519,14 +528,14 @@ template <> struct SizePlan<double, 324> {
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<double, 360> {
-  using X = LinePlanD<360, 48, Radices<10, 4, 9>, Radices<9, 4, 10>>;
+  using X = LinePlanD<360, 72, Radices<6, 5, 2, 6>, Radices<6, 2, 5, 6>>;
   using Y = LinePlanD<360, 48, Radices<10, 4, 9>, Radices<9, 4, 10>>;
   using Z = LinePlanD<360, 64, Radices<10, 6, 6>, Radices<6, 6, 10>>;
   using ZA = LinePlanD<360, 64, Radices<10, 6, 6>, Radices<6, 6, 10>>;
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<double, 384> {
-  using X = LinePlanD<384, 64, Radices<8, 6, 8>, Radices<8, 6, 8>>;
+  using X = LinePlanD<384, 64, Radices<6, 8, 8>, Radices<8, 8, 6>>;
   using Y = LinePlanD<384, 64, Radices<8, 6, 8>, Radices<8, 6, 8>>;
   using Z = LinePlanD<384, 64, Radices<8, 6, 8>, Radices<8, 6, 8>>;
   using ZA = LinePlanD<384, 64, Radices<8, 6, 8>, Radices<8, 6, 8>>;
@@ -540,14 +549,14 @@ template <> struct SizePlan<double, 400> {
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<double, 432> {
-  using X = LinePlanD<432, 56, Radices<9, 4, 4, 3>, Radices<3, 4, 4, 9>>;
+  using X = LinePlanD<432, 72, Radices<6, 6, 2, 6>, Radices<6, 2, 6, 6>>;
   using Y = LinePlanD<432, 56, Radices<9, 4, 4, 3>, Radices<3, 4, 4, 9>>;
   using Z = LinePlanD<432, 64, Radices<12, 4, 9>, Radices<9, 4, 12>>;
   using ZA = LinePlanD<432, 64, Radices<12, 4, 9>, Radices<9, 4, 12>>;
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<double, 450> {
-  using X = LinePlanD<450, 56, Radices<10, 9, 5>, Radices<5, 9, 10>>;
+  using X = LinePlanD<450, 90, Radices<6, 5, 5, 3>, Radices<3, 5, 5, 6>>;
   using Y = LinePlanD<450, 56, Radices<10, 9, 5>, Radices<5, 9, 10>>;
   using Z = LinePlanD<450, 64, Radices<10, 9, 5>, Radices<5, 9, 10>>;
   using ZA = LinePlanD<450, 64, Radices<10, 9, 5>, Radices<5, 9, 10>>;

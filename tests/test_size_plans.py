@@ -46,7 +46,7 @@ def test_size_plan(typ, n, plans, pz, pza):
         assert np.abs(_run_plan(n, tpl, inv, +1, x) - np.fft.ifft(x) * n).max() <= 1e-12 * np.abs(x).sum()
         assert np.abs(_run_plan(n, tpl, fwd, -1, x) - np.fft.fft(x)).max() <= 1e-12 * np.abs(x).sum()
     for i, (kind, m, tpl, inv, fwd) in enumerate(plans[:2]):   # x and y tiles
-        assert tpl * cols <= (512 if i == 0 else 1024) and tpl * cols % 64 == 0
+        assert tpl * cols <= 1024  # one thread block
         assert elem * (n * (cols + 1) + 3 * n + 2 * cols) <= 160 * 1024
     for (kind, m, tpl, inv, fwd), lines in ((plans[2], pz), (plans[3], pza)):
         assert 64 % tpl == 0 and tpl * lines % 64 == 0 and tpl * lines <= 1024 and n * n % lines == 0
