@@ -19,11 +19,14 @@
 // a line (to 64 threads in FP32, 128 in FP64; EPT at most 12 and 10), PS-RK2 random and
 // RK4 steps and the gradient, and replaced where the steps were 1.5% faster or more: the x
 // passes of FP32 want more threads a line and 5 to 10 registers a transform than the
-// estimate gave (their x-forward kernel holds operands for every stage).  Random steps, us:
+// estimate gave (their x-forward kernel holds operands for every stage).  From N = 48 on the
+// y and z plans were timed against three others and replaced where their pass was 4% faster.  Random steps, us:
 // 100^3 10 10 over 12 to 5 4 5 over 25 131 -> 114, 150^3 3 5 10 over 16 to 6 5 5
 // over 32 approx 285 -> 244, 288^3 2 12 12 over 24 to 6 6 8 over 48 1690 -> 1530, 500^3
 // 5 10 10 over 28 to 10 5 10 over 50 13.4 -> 10.3 ms; FP64 384^3 8 6 8 to 6 8 8 over 64 6.40 ->
-// 6.07 ms.
+// 6.07 ms; y passes, us: 400^3 4 10 10 over 40 to 32 threads 16 5 5 956 -> 706, FP64 360^3 10 4
+// 9 over 48 to 10 6 6 over 60 1299 -> 953; z passes: 200^3 5 4 10 over 32 to 8 5 5 over 16 92 ->
+// 72, FP64 240^3 8 5 6 to 3 4 4 5 over 64 276 -> 217.
 //
 // Against the size-generic passes these sizes ran before (LDS Stockham stages over a
 // runtime plan: an LDS round trip and two barriers a radix, index divisions, shift
@@ -110,9 +113,9 @@ template <> struct SizePlan<float, 50> {
 template <> struct SizePlan<float, 54> {
   using X = LinePlan<54, 18, Radices<6, 3, 3>, Radices<3, 3, 6>>;
   using Y = LinePlan<54, 20, Radices<6, 3, 3>, Radices<3, 3, 6>>;
-  using Z = LinePlan<54, 32, Radices<6, 3, 3>, Radices<3, 3, 6>>;
+  using Z = LinePlan<54, 32, Radices<3, 2, 3, 3>, Radices<3, 3, 2, 3>>;
   using ZA = LinePlan<54, 32, Radices<6, 3, 3>, Radices<3, 3, 6>>;
-  static constexpr int PZ = 4, PZA = 4;
+  static constexpr int PZ = 2, PZA = 4;
 };
 template <> struct SizePlan<float, 60> {
   using X = LinePlan<60, 20, Radices<5, 3, 4>, Radices<4, 3, 5>>;
@@ -124,9 +127,9 @@ template <> struct SizePlan<float, 60> {
 template <> struct SizePlan<float, 72> {
   using X = LinePlan<72, 36, Radices<4, 2, 3, 3>, Radices<3, 3, 2, 4>>;
   using Y = LinePlan<72, 24, Radices<6, 3, 4>, Radices<4, 3, 6>>;
-  using Z = LinePlan<72, 64, Radices<4, 2, 3, 3>, Radices<3, 3, 2, 4>>;
+  using Z = LinePlan<72, 32, Radices<6, 3, 4>, Radices<4, 3, 6>>;
   using ZA = LinePlan<72, 64, Radices<4, 2, 3, 3>, Radices<3, 3, 2, 4>>;
-  static constexpr int PZ = 4, PZA = 4;
+  static constexpr int PZ = 2, PZA = 4;
 };
 template <> struct SizePlan<float, 80> {
   using X = LinePlan<80, 20, Radices<5, 4, 4>, Radices<4, 4, 5>>;
@@ -152,9 +155,9 @@ template <> struct SizePlan<float, 96> {
 template <> struct SizePlan<float, 100> {
   using X = LinePlan<100, 25, Radices<5, 4, 5>, Radices<5, 4, 5>>;
   using Y = LinePlan<100, 12, Radices<10, 10>, Radices<10, 10>>;
-  using Z = LinePlan<100, 16, Radices<10, 10>, Radices<10, 10>>;
+  using Z = LinePlan<100, 32, Radices<5, 4, 5>, Radices<5, 4, 5>>;
   using ZA = LinePlan<100, 16, Radices<10, 10>, Radices<10, 10>>;
-  static constexpr int PZ = 16, PZA = 16;
+  static constexpr int PZ = 2, PZA = 16;
 };
 template <> struct SizePlan<float, 108> {
   using X = LinePlan<108, 32, Radices<3, 6, 6>, Radices<6, 6, 3>>;
@@ -166,9 +169,9 @@ template <> struct SizePlan<float, 108> {
 template <> struct SizePlan<float, 120> {
   using X = LinePlan<120, 12, Radices<10, 12>, Radices<12, 10>>;
   using Y = LinePlan<120, 12, Radices<12, 10>, Radices<10, 12>>;
-  using Z = LinePlan<120, 16, Radices<10, 4, 3>, Radices<3, 4, 10>>;
+  using Z = LinePlan<120, 32, Radices<6, 4, 5>, Radices<5, 4, 6>>;
   using ZA = LinePlan<120, 32, Radices<6, 4, 5>, Radices<5, 4, 6>>;
-  static constexpr int PZ = 16, PZA = 8;
+  static constexpr int PZ = 2, PZA = 8;
 };
 template <> struct SizePlan<float, 150> {
   using X = LinePlan<150, 32, Radices<6, 5, 5>, Radices<5, 5, 6>>;
@@ -194,16 +197,16 @@ template <> struct SizePlan<float, 180> {
 template <> struct SizePlan<float, 200> {
   using X = LinePlan<200, 50, Radices<5, 2, 4, 5>, Radices<5, 4, 2, 5>>;
   using Y = LinePlan<200, 20, Radices<2, 10, 10>, Radices<10, 10, 2>>;
-  using Z = LinePlan<200, 32, Radices<5, 4, 10>, Radices<10, 4, 5>>;
+  using Z = LinePlan<200, 16, Radices<8, 5, 5>, Radices<5, 5, 8>>;
   using ZA = LinePlan<200, 32, Radices<5, 4, 10>, Radices<10, 4, 5>>;
-  static constexpr int PZ = 8, PZA = 8;
+  static constexpr int PZ = 4, PZA = 8;
 };
 template <> struct SizePlan<float, 250> {
   using X = LinePlan<250, 50, Radices<2, 5, 5, 5>, Radices<5, 5, 5, 2>>;
   using Y = LinePlan<250, 28, Radices<5, 5, 10>, Radices<10, 5, 5>>;
-  using Z = LinePlan<250, 32, Radices<5, 5, 10>, Radices<10, 5, 5>>;
+  using Z = LinePlan<250, 64, Radices<5, 2, 5, 5>, Radices<5, 5, 2, 5>>;
   using ZA = LinePlan<250, 32, Radices<5, 5, 10>, Radices<10, 5, 5>>;
-  static constexpr int PZ = 4, PZA = 4;
+  static constexpr int PZ = 2, PZA = 4;
 };
 template <> struct SizePlan<float, 288> {
   using X = LinePlan<288, 48, Radices<6, 6, 8>, Radices<8, 6, 6>>;
@@ -228,21 +231,21 @@ template <> struct SizePlan<float, 320> {
 };
 template <> struct SizePlan<float, 400> {
   using X = LinePlan<400, 40, Radices<10, 10, 4>, Radices<4, 10, 10>>;
-  using Y = LinePlan<400, 40, Radices<4, 10, 10>, Radices<10, 10, 4>>;
-  using Z = LinePlan<400, 64, Radices<10, 4, 10>, Radices<10, 4, 10>>;
+  using Y = LinePlan<400, 32, Radices<16, 5, 5>, Radices<5, 5, 16>>;
+  using Z = LinePlan<400, 32, Radices<16, 5, 5>, Radices<5, 5, 16>>;
   using ZA = LinePlan<400, 64, Radices<10, 4, 10>, Radices<10, 4, 10>>;
-  static constexpr int PZ = 4, PZA = 4;
+  static constexpr int PZ = 2, PZA = 4;
 };
 template <> struct SizePlan<float, 432> {
   using X = LinePlan<432, 54, Radices<3, 4, 4, 9>, Radices<9, 4, 4, 3>>;
-  using Y = LinePlan<432, 36, Radices<3, 12, 12>, Radices<12, 12, 3>>;
+  using Y = LinePlan<432, 32, Radices<16, 3, 3, 3>, Radices<3, 3, 3, 16>>;
   using Z = LinePlan<432, 64, Radices<3, 4, 4, 9>, Radices<9, 4, 4, 3>>;
   using ZA = LinePlan<432, 64, Radices<3, 4, 4, 9>, Radices<9, 4, 4, 3>>;
   static constexpr int PZ = 4, PZA = 4;
 };
 template <> struct SizePlan<float, 450> {
   using X = LinePlan<450, 45, Radices<3, 5, 10, 3>, Radices<3, 10, 5, 3>>;
-  using Y = LinePlan<450, 52, Radices<5, 9, 10>, Radices<10, 9, 5>>;
+  using Y = LinePlan<450, 45, Radices<3, 5, 10, 3>, Radices<3, 10, 5, 3>>;
   using Z = LinePlan<450, 64, Radices<5, 9, 10>, Radices<10, 9, 5>>;
   using ZA = LinePlan<450, 64, Radices<5, 9, 10>, Radices<10, 9, 5>>;
   static constexpr int PZ = 4, PZA = 4;
@@ -250,9 +253,9 @@ template <> struct SizePlan<float, 450> {
 template <> struct SizePlan<float, 480> {
   using X = LinePlan<480, 32, Radices<4, 3, 5, 8>, Radices<8, 5, 3, 4>>;
   using Y = LinePlan<480, 48, Radices<4, 10, 12>, Radices<12, 10, 4>>;
-  using Z = LinePlan<480, 64, Radices<10, 4, 4, 3>, Radices<3, 4, 4, 10>>;
+  using Z = LinePlan<480, 64, Radices<5, 4, 8, 3>, Radices<3, 8, 4, 5>>;
   using ZA = LinePlan<480, 64, Radices<10, 4, 4, 3>, Radices<3, 4, 4, 10>>;
-  static constexpr int PZ = 4, PZA = 4;
+  static constexpr int PZ = 2, PZA = 4;
 };
 template <> struct SizePlan<float, 486> {
   using X = LinePlan<486, 64, Radices<3, 9, 2, 9>, Radices<9, 2, 9, 3>>;
@@ -341,9 +344,9 @@ template <> struct SizePlan<double, 50> {
 template <> struct SizePlan<double, 54> {
   using X = LinePlanD<54, 24, Radices<6, 3, 3>, Radices<3, 3, 6>>;
   using Y = LinePlanD<54, 24, Radices<6, 3, 3>, Radices<3, 3, 6>>;
-  using Z = LinePlanD<54, 32, Radices<6, 3, 3>, Radices<3, 3, 6>>;
+  using Z = LinePlanD<54, 32, Radices<3, 2, 3, 3>, Radices<3, 3, 2, 3>>;
   using ZA = LinePlanD<54, 32, Radices<6, 3, 3>, Radices<3, 3, 6>>;
-  static constexpr int PZ = 4, PZA = 4;
+  static constexpr int PZ = 2, PZA = 4;
 };
 template <> struct SizePlan<double, 60> {
   using X = LinePlanD<60, 24, Radices<5, 3, 4>, Radices<4, 3, 5>>;
@@ -369,9 +372,9 @@ template <> struct SizePlan<double, 72> {
 template <> struct SizePlan<double, 80> {
   using X = LinePlanD<80, 24, Radices<5, 4, 4>, Radices<4, 4, 5>>;
   using Y = LinePlanD<80, 24, Radices<5, 4, 4>, Radices<4, 4, 5>>;
-  using Z = LinePlanD<80, 32, Radices<5, 4, 4>, Radices<4, 4, 5>>;
+  using Z = LinePlanD<80, 32, Radices<4, 4, 5>, Radices<5, 4, 4>>;
   using ZA = LinePlanD<80, 32, Radices<5, 4, 4>, Radices<4, 4, 5>>;
-  static constexpr int PZ = 8, PZA = 8;
+  static constexpr int PZ = 2, PZA = 8;
 };
 template <> struct SizePlan<double, 90> {
   using X = LinePlanD<90, 32, Radices<6, 3, 5>, Radices<5, 3, 6>>;
@@ -382,14 +385,14 @@ template <> struct SizePlan<double, 90> {
 };
 template <> struct SizePlan<double, 96> {
   using X = LinePlanD<96, 24, Radices<4, 4, 6>, Radices<6, 4, 4>>;
-  using Y = LinePlanD<96, 16, Radices<8, 2, 6>, Radices<6, 2, 8>>;
-  using Z = LinePlanD<96, 16, Radices<8, 2, 6>, Radices<6, 2, 8>>;
+  using Y = LinePlanD<96, 24, Radices<6, 4, 4>, Radices<4, 4, 6>>;
+  using Z = LinePlanD<96, 32, Radices<4, 2, 3, 4>, Radices<4, 3, 2, 4>>;
   using ZA = LinePlanD<96, 16, Radices<8, 2, 6>, Radices<6, 2, 8>>;
-  static constexpr int PZ = 16, PZA = 16;
+  static constexpr int PZ = 2, PZA = 16;
 };
 template <> struct SizePlan<double, 100> {
   using X = LinePlanD<100, 32, Radices<5, 4, 5>, Radices<5, 4, 5>>;
-  using Y = LinePlanD<100, 16, Radices<10, 10>, Radices<10, 10>>;
+  using Y = LinePlanD<100, 25, Radices<5, 4, 5>, Radices<5, 4, 5>>;
   using Z = LinePlanD<100, 32, Radices<5, 4, 5>, Radices<5, 4, 5>>;
   using ZA = LinePlanD<100, 32, Radices<5, 4, 5>, Radices<5, 4, 5>>;
   static constexpr int PZ = 8, PZA = 8;
@@ -397,9 +400,9 @@ template <> struct SizePlan<double, 100> {
 template <> struct SizePlan<double, 108> {
   using X = LinePlanD<108, 24, Radices<6, 3, 6>, Radices<6, 3, 6>>;
   using Y = LinePlanD<108, 16, Radices<9, 4, 3>, Radices<3, 4, 9>>;
-  using Z = LinePlanD<108, 32, Radices<6, 3, 6>, Radices<6, 3, 6>>;
+  using Z = LinePlanD<108, 16, Radices<9, 4, 3>, Radices<3, 4, 9>>;
   using ZA = LinePlanD<108, 16, Radices<9, 4, 3>, Radices<3, 4, 9>>;
-  static constexpr int PZ = 8, PZA = 16;
+  static constexpr int PZ = 4, PZA = 16;
 };
 template <> struct SizePlan<double, 120> {
   using X = LinePlanD<120, 30, Radices<5, 4, 6>, Radices<6, 4, 5>>;
@@ -432,13 +435,13 @@ template <> struct SizePlan<double, 150> {
 template <> struct SizePlan<double, 160> {
   using X = LinePlanD<160, 40, Radices<5, 2, 4, 4>, Radices<4, 4, 2, 5>>;
   using Y = LinePlanD<160, 32, Radices<8, 5, 4>, Radices<4, 5, 8>>;
-  using Z = LinePlanD<160, 32, Radices<8, 5, 4>, Radices<4, 5, 8>>;
+  using Z = LinePlanD<160, 32, Radices<4, 5, 8>, Radices<8, 5, 4>>;
   using ZA = LinePlanD<160, 32, Radices<8, 5, 4>, Radices<4, 5, 8>>;
-  static constexpr int PZ = 8, PZA = 8;
+  static constexpr int PZ = 2, PZA = 8;
 };
 template <> struct SizePlan<double, 162> {
   using X = LinePlanD<162, 27, Radices<6, 3, 3, 3>, Radices<3, 3, 3, 6>>;
-  using Y = LinePlanD<162, 24, Radices<9, 2, 9>, Radices<9, 2, 9>>;
+  using Y = LinePlanD<162, 27, Radices<9, 3, 6>, Radices<6, 3, 9>>;
   using Z = LinePlanD<162, 32, Radices<6, 3, 3, 3>, Radices<3, 3, 3, 6>>;
   using ZA = LinePlanD<162, 32, Radices<9, 3, 6>, Radices<6, 3, 9>>;
   static constexpr int PZ = 4, PZA = 4;
@@ -466,17 +469,17 @@ template <> struct SizePlan<double, 200> {
 };
 template <> struct SizePlan<double, 216> {
   using X = LinePlanD<216, 40, Radices<6, 6, 6>, Radices<6, 6, 6>>;
-  using Y = LinePlanD<216, 40, Radices<6, 6, 6>, Radices<6, 6, 6>>;
-  using Z = LinePlanD<216, 64, Radices<6, 6, 6>, Radices<6, 6, 6>>;
+  using Y = LinePlanD<216, 18, Radices<12, 3, 6>, Radices<6, 3, 12>>;
+  using Z = LinePlanD<216, 32, Radices<9, 8, 3>, Radices<3, 8, 9>>;
   using ZA = LinePlanD<216, 32, Radices<9, 8, 3>, Radices<3, 8, 9>>;
-  static constexpr int PZ = 4, PZA = 8;
+  static constexpr int PZ = 2, PZA = 8;
 };
 template <> struct SizePlan<double, 240> {
   using X = LinePlanD<240, 64, Radices<3, 4, 4, 5>, Radices<5, 4, 4, 3>>;
   using Y = LinePlanD<240, 32, Radices<10, 8, 3>, Radices<3, 8, 10>>;
-  using Z = LinePlanD<240, 64, Radices<8, 5, 6>, Radices<6, 5, 8>>;
+  using Z = LinePlanD<240, 64, Radices<3, 4, 4, 5>, Radices<5, 4, 4, 3>>;
   using ZA = LinePlanD<240, 32, Radices<10, 8, 3>, Radices<3, 8, 10>>;
-  static constexpr int PZ = 4, PZA = 8;
+  static constexpr int PZ = 2, PZA = 8;
 };
 template <> struct SizePlan<double, 250> {
   using X = LinePlanD<250, 50, Radices<5, 5, 10>, Radices<10, 5, 5>>;
@@ -501,7 +504,7 @@ template <> struct SizePlan<double, 270> {
 };
 template <> struct SizePlan<double, 288> {
   using X = LinePlanD<288, 48, Radices<6, 6, 8>, Radices<8, 6, 6>>;
-  using Y = LinePlanD<288, 40, Radices<9, 4, 8>, Radices<8, 4, 9>>;
+  using Y = LinePlanD<288, 24, Radices<12, 2, 12>, Radices<12, 2, 12>>;
   using Z = LinePlanD<288, 64, Radices<8, 6, 6>, Radices<6, 6, 8>>;
   using ZA = LinePlanD<288, 64, Radices<8, 6, 6>, Radices<6, 6, 8>>;
   static constexpr int PZ = 4, PZA = 4;
@@ -515,7 +518,7 @@ template <> struct SizePlan<double, 300> {
 };
 template <> struct SizePlan<double, 320> {
   using X = LinePlanD<320, 80, Radices<4, 4, 4, 5>, Radices<5, 4, 4, 4>>;
-  using Y = LinePlanD<320, 40, Radices<10, 4, 8>, Radices<8, 4, 10>>;
+  using Y = LinePlanD<320, 80, Radices<5, 4, 4, 4>, Radices<4, 4, 4, 5>>;
   using Z = LinePlanD<320, 64, Radices<8, 5, 8>, Radices<8, 5, 8>>;
   using ZA = LinePlanD<320, 64, Radices<8, 5, 8>, Radices<8, 5, 8>>;
   static constexpr int PZ = 4, PZA = 4;
@@ -529,10 +532,10 @@ template <> struct SizePlan<double, 324> {
 };
 template <> struct SizePlan<double, 360> {
   using X = LinePlanD<360, 72, Radices<6, 5, 2, 6>, Radices<6, 2, 5, 6>>;
-  using Y = LinePlanD<360, 48, Radices<10, 4, 9>, Radices<9, 4, 10>>;
-  using Z = LinePlanD<360, 64, Radices<10, 6, 6>, Radices<6, 6, 10>>;
+  using Y = LinePlanD<360, 60, Radices<10, 6, 6>, Radices<6, 6, 10>>;
+  using Z = LinePlanD<360, 64, Radices<6, 6, 10>, Radices<10, 6, 6>>;
   using ZA = LinePlanD<360, 64, Radices<10, 6, 6>, Radices<6, 6, 10>>;
-  static constexpr int PZ = 4, PZA = 4;
+  static constexpr int PZ = 2, PZA = 4;
 };
 template <> struct SizePlan<double, 384> {
   using X = LinePlanD<384, 64, Radices<6, 8, 8>, Radices<8, 8, 6>>;
@@ -543,7 +546,7 @@ template <> struct SizePlan<double, 384> {
 };
 template <> struct SizePlan<double, 400> {
   using X = LinePlanD<400, 56, Radices<10, 4, 10>, Radices<10, 4, 10>>;
-  using Y = LinePlanD<400, 40, Radices<10, 2, 2, 10>, Radices<10, 2, 2, 10>>;
+  using Y = LinePlanD<400, 50, Radices<10, 4, 10>, Radices<10, 4, 10>>;
   using Z = LinePlanD<400, 64, Radices<10, 4, 10>, Radices<10, 4, 10>>;
   using ZA = LinePlanD<400, 64, Radices<10, 4, 10>, Radices<10, 4, 10>>;
   static constexpr int PZ = 4, PZA = 4;
@@ -551,16 +554,16 @@ template <> struct SizePlan<double, 400> {
 template <> struct SizePlan<double, 432> {
   using X = LinePlanD<432, 72, Radices<6, 6, 2, 6>, Radices<6, 2, 6, 6>>;
   using Y = LinePlanD<432, 56, Radices<9, 4, 4, 3>, Radices<3, 4, 4, 9>>;
-  using Z = LinePlanD<432, 64, Radices<12, 4, 9>, Radices<9, 4, 12>>;
+  using Z = LinePlanD<432, 64, Radices<3, 4, 4, 9>, Radices<9, 4, 4, 3>>;
   using ZA = LinePlanD<432, 64, Radices<12, 4, 9>, Radices<9, 4, 12>>;
-  static constexpr int PZ = 4, PZA = 4;
+  static constexpr int PZ = 2, PZA = 4;
 };
 template <> struct SizePlan<double, 450> {
   using X = LinePlanD<450, 90, Radices<6, 5, 5, 3>, Radices<3, 5, 5, 6>>;
   using Y = LinePlanD<450, 56, Radices<10, 9, 5>, Radices<5, 9, 10>>;
-  using Z = LinePlanD<450, 64, Radices<10, 9, 5>, Radices<5, 9, 10>>;
+  using Z = LinePlanD<450, 64, Radices<5, 9, 10>, Radices<10, 9, 5>>;
   using ZA = LinePlanD<450, 64, Radices<10, 9, 5>, Radices<5, 9, 10>>;
-  static constexpr int PZ = 4, PZA = 4;
+  static constexpr int PZ = 2, PZA = 4;
 };
 template <> struct SizePlan<double, 480> {
   using X = LinePlanD<480, 64, Radices<10, 4, 4, 3>, Radices<3, 4, 4, 10>>;
@@ -581,7 +584,7 @@ template <> struct SizePlan<double, 500> {
   using Y = LinePlanD<500, 56, Radices<10, 5, 10>, Radices<10, 5, 10>>;
   using Z = LinePlanD<500, 64, Radices<10, 5, 10>, Radices<10, 5, 10>>;
   using ZA = LinePlanD<500, 64, Radices<10, 5, 10>, Radices<10, 5, 10>>;
-  static constexpr int PZ = 4, PZA = 4;
+  static constexpr int PZ = 2, PZA = 4;
 };
 template <> struct SizePlan<double, 512> {
   using X = LinePlanD<512, 64, Radices<8, 8, 8>, Radices<8, 8, 8>>;
