@@ -1,4 +1,5 @@
-// ns_fast.hpp -- compile-time specialised passes for the common grid sizes (FP32, gfx950).
+// ns_fast.hpp -- compile-time specialised passes (gfx950): every grid size from 16 to 512 in
+// FP32 and FP64; the plans of thirteen FP32 sizes are below, the others in ns_size_plans.hpp.
 //
 // Same scratch layout, tile list and pass semantics as the generic kernels of
 // ns_kernels.hpp, except that in the step sequences the x-inverse passes store
@@ -7,7 +8,8 @@
 // exchange per radix boundary instead of one LDS round trip per stage, and all
 // indices are compile-time except the thread and block coordinates.
 //
-// Strided passes (x, y): a block is one tile of L = 16 contiguous k_z columns;
+// Strided passes (x, y): a block is one tile of L contiguous k_z columns (16 in FP32, 8
+// in FP64: 128-byte rows);
 // thread (l, t) = (tid mod L, tid div L) handles column l, points of the line
 // owned by t.  LDS: the exchange buffer [position][column] (row pitch L + 1 to
 // spread banks) and the twiddle table.
@@ -27,7 +29,6 @@ namespace ns {
 // k_z columns of a tile of the strided passes: one 128-byte row of the scratch fields
 template <typename T>
 constexpr int tile_cols() { return 128 / (2 * (int)sizeof(T)); }
-constexpr int kFastL = tile_cols<float>();
 
 // Addressing: a block-uniform base pointer (a state component or scratch field)
 // plus a per-lane 32-bit element offset.  Every offset stays inside one component
@@ -848,12 +849,12 @@ using LP256b = LinePlan<256, 32, Radices<8, 8, 4>, Radices<4, 8, 8>>;
 // of PS-RK2 random steps, us: 64^3 8 8 over 8 threads 17.6, 4 4 4 over 16 15.6; 128^3 8 4
 // 4 over 16 24.5, 4 8 4 over 32 22.8; 144^3 12 12 over 12 27.1, 6 6 4 over 24 25.9; 160^3
 // 10 4 4 over 16 34.0, 5 8 4 over 32 29.4; 192^3 12 4 4 over 16 65, 6 8 4 over 32 63 (RK4
-// 34.4, 31.7); 324^3 12 3 3 3 over 27 343, 6 6
-// 9 over 54 308; 360^3 12 6 5 over 30 469, 6 10 6 over 60 443; 384^3 12 4 4 2 over 32
-// 507, 8 6 8 over 48 456.  216, 240, 256 and 512 had no better plan (256^3 4 4 4 4 over 64:
-// 163 against 165, but 91 against 86 in RK4).  270 keeps 9 6 5 over 30 threads: 5 6 9 over 54
-// made the fused pass 154 -> 140, but f_xinv 74 -> 85 and the last stage 121 -> 126.  f_xinv and f_xfwd
-// run one plan, so that chained and single evaluations agree bit for bit.
+// 34.4, 31.7); 324^3 12 3 3 3 over 27 343, 6 6 9 over 54 308; 360^3 12 6 5 over 30 469, 6
+// 10 6 over 60 443; 384^3 12 4 4 2 over 32 507, 8 6 8 over 48 456.  216, 240, 256 and 512
+// had no better plan (256^3 4 4 4 4 over 64: 163 against 165, but 91 against 86 in RK4).
+// 270 keeps 9 6 5 over 30 threads: 5 6 9 over 54 made the fused pass 154 -> 140, but
+// f_xinv 74 -> 85 and the last stage 121 -> 126.  f_xinv and f_xfwd run one plan, so that
+// chained and single evaluations agree bit for bit.
 using LP64x = LinePlan<64, 16, Radices<4, 4, 4>, Radices<4, 4, 4>>;
 using Fast64 = FastCfg<LP64x, LP64, LP64, 16, XPass<LP64x, 2>>;
 using LP128x = LinePlan<128, 32, Radices<4, 8, 4>, Radices<4, 8, 4>>;
