@@ -56,13 +56,13 @@ k_xlam(LamArgs<R> la, Cx<R>* __restrict__ W, const Cx<R>* __restrict__ twg, Shif
       const int p = e >> g.lgL, l = e & (L - 1);
       const int kz = kz0 + l, kx = kval(p, n);
       if (kz < g.kzn && retained(g, kx, ky, kz)) {
-        const long long ia = lay_at(la.la, p, yi, kz, n);
+        const long long ia = row_at(la.la, p, yi, kz, n);
         const long long k2 = (long long)kx * kx + (long long)ky * ky + (long long)kz * kz;
         R fa = la.cA * (la.eA ? la.eA[k2] : R(1));
         Cx<R> q[3];
         for (int c = 0; c < 3; ++c) q[c] = scale(la.A[c * la.la.cs + ia], fa);
         if (la.B != nullptr) {
-          const long long ib = lay_at(la.lb, p, yi, kz, n);
+          const long long ib = row_at(la.lb, p, yi, kz, n);
           const R fb = la.cB * (la.eB ? la.eB[k2] : R(1));
           for (int c = 0; c < 3; ++c) q[c] = q[c] + scale(la.B[c * la.lb.cs + ib], fb);
         }
@@ -293,14 +293,14 @@ k_xadj(const Cx<R>* __restrict__ W, const Cx<R>* __restrict__ twg, Shift sh,
     const int kz = kz0 + l;
     if (kz >= g.h || (!a.full && kz >= g.kzn)) continue;
     const int kx = kval(p, n);
-    const long long io0 = lay_at(a.lo0, p, yi, kz, n);
+    const long long io0 = row_at(a.lo0, p, yi, kz, n);
     const bool ret = active && kz < g.kzn && retained(g, kx, ky, kz);
     if (!ret) {
       if (a.full)
         for (int c = 0; c < 3; ++c) a.out0[c * a.lo0.cs + io0] = cx(R(0), R(0));
       continue;
     }
-    const long long ii0 = lay_at(a.li0, p, yi, kz, n), ii1 = lay_at(a.li1, p, yi, kz, n);
+    const long long ii0 = row_at(a.li0, p, yi, kz, n), ii1 = row_at(a.li1, p, yi, kz, n);
     Cx<R> V[3] = {scale(r[0][i], inv_n3), scale(r[1][i], inv_n3), scale(r[2][i], inv_n3)};
     if (sh.on) {
       const Cx<R> phi = cmul(cmul(phx[p], phase1<R>(ky, sh.s[1], n)), phase1<R>(kz, sh.s[2], n));

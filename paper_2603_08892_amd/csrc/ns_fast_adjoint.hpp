@@ -51,12 +51,12 @@ f_xlam(LamArgs<typename C::T> la, Cx<typename C::T>* __restrict__ W, const Cx<ty
     const bool ok = col && F::in_ok(t, i) && keep(kx);
     const int k2 = ok ? kx * kx + ky * ky + kz * kz : 0;
     const T fa = la.cA * (la.eA ? la.eA[k2] : T(1));
-    const uint32_t ia = (uint32_t)((p * N + yi) * la.la.pitch + p * la.la.pad + kz);
+    const uint32_t ia = (uint32_t)((p * N + yi) * la.la.pitch + p * pad_of<C>(la.la.pad) + kz);
 #pragma unroll
     for (int c = 0; c < 3; ++c) q[c][i] = scale(ld_masked(la.A + c * la.la.cs, ia, ok), fa);
     if (la.B != nullptr) {
       const T fb = la.cB * (la.eB ? la.eB[k2] : T(1));
-      const uint32_t ib = (uint32_t)((p * N + yi) * la.lb.pitch + p * la.lb.pad + kz);
+      const uint32_t ib = (uint32_t)((p * N + yi) * la.lb.pitch + p * pad_of<C>(la.lb.pad) + kz);
 #pragma unroll
       for (int c = 0; c < 3; ++c) q[c][i] = q[c][i] + scale(ld_masked(la.B + c * la.lb.cs, ib, ok), fb);
     }
@@ -76,7 +76,7 @@ f_xlam(LamArgs<typename C::T> la, Cx<typename C::T>* __restrict__ W, const Cx<ty
       for (int c = 0; c < 3; ++c) q[c][i] = cmul(q[c][i], phi);
     }
   }
-  const uint32_t obase = (uint32_t)(yi * g.kzp + kz0) + l, ostep = (uint32_t)(N * g.kzp + g.pad);
+  const uint32_t obase = (uint32_t)(yi * g.kzp + kz0) + l, ostep = (uint32_t)(N * g.kzp + pad_of<C>(g.pad));
 #pragma unroll
   for (int f = 0; f < 3; ++f) {
     F::run(q[f], t, lv, tw);
@@ -114,7 +114,7 @@ f_zadj(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
   for (int i = tid; i < N; i += NT) tw[i] = twg[i];
   __syncthreads();  // the transforms below synchronise only within a wavefront
   const LineView<T, 1> lv{xb + p * LP};
-  const uint32_t lbase = line * (uint32_t)g.kzp + (line / N) * (uint32_t)g.pad;
+  const uint32_t lbase = line * (uint32_t)g.kzp + (line / N) * (uint32_t)pad_of<C>(g.pad);
   Cx<T> z[4][EPT], v[EPT];
 #pragma unroll
   for (int q = 0; q < 5; ++q) {
@@ -209,7 +209,7 @@ f_xadj(const Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restr
       phase_cols(phc, ky, kz0, sh, N, tid);
     }
     const bool col = kz < g.kzn;
-    const uint32_t wbase = (uint32_t)(yi * g.kzp + kz0) + l, wstep = (uint32_t)(N * g.kzp + g.pad);
+    const uint32_t wbase = (uint32_t)(yi * g.kzp + kz0) + l, wstep = (uint32_t)(N * g.kzp + pad_of<C>(g.pad));
     const T kyf = T(ky), kzf = T(kz);
 #pragma unroll
     for (int f = 0; f < 6; ++f) {
@@ -247,7 +247,7 @@ f_xadj(const Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restr
     if (!F::out_ok(t, i)) continue;  // no point in this register
     const int p = F::out_pos(t, i);
     const int kx = kval(p, N);
-    const uint32_t io0 = (uint32_t)((p * N + yi) * a.lo0.pitch + p * a.lo0.pad + kz);
+    const uint32_t io0 = (uint32_t)((p * N + yi) * a.lo0.pitch + p * pad_of<C>(a.lo0.pad) + kz);
     if (!(line_kept && keep(kx))) {
       if (a.full)
         for (int c = 0; c < 3; ++c) st_off(a.out0 + c * a.lo0.cs, io0, cx(T(0), T(0)));
@@ -261,8 +261,8 @@ f_xadj(const Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restr
     }
     const int k2 = kx * kx + ky * ky + kz * kz;
     const T eh = a.eh[k2], edt = a.edt[k2];
-    const uint32_t ii0 = (uint32_t)((p * N + yi) * a.li0.pitch + p * a.li0.pad + kz);
-    const uint32_t ii1 = (uint32_t)((p * N + yi) * a.li1.pitch + p * a.li1.pad + kz);
+    const uint32_t ii0 = (uint32_t)((p * N + yi) * a.li0.pitch + p * pad_of<C>(a.li0.pad) + kz);
+    const uint32_t ii1 = (uint32_t)((p * N + yi) * a.li1.pitch + p * pad_of<C>(a.li1.pad) + kz);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       Cx<T>* out0 = a.out0 + c * a.lo0.cs;

@@ -89,6 +89,11 @@ struct Lay {
 __device__ __forceinline__ long long lay_at(const Lay& L, int xi, int yi, int kz, int n) {
   return ((long long)xi * n + yi) * L.pitch + (long long)xi * L.pad + kz;
 }
+// The same in the size-generic passes, whose layouts are never padded (the term cost 0.3% of
+// a call at 540^3).
+__device__ __forceinline__ long long row_at(const Lay& L, int xi, int yi, int kz, int n) {
+  return ((long long)xi * n + yi) * L.pitch + kz;
+}
 
 // Grid shift s (grid-spacing units); on == 0: unshifted.
 struct Shift {
@@ -140,7 +145,7 @@ k_xinv(const Cx<R>* __restrict__ S, Lay ls, Cx<R>* __restrict__ W, const Cx<R>* 
       const int p = e >> g.lgL, l = e & (L - 1);
       const int kz = kz0 + l, kx = kval(p, n);
       if (kz < g.kzn && retained(g, kx, ky, kz)) {
-        const long long idx = lay_at(ls, p, yi, kz, n);
+        const long long idx = row_at(ls, p, yi, kz, n);
         u[0][i] = S[idx];
         u[1][i] = S[ls.cs + idx];
         u[2][i] = S[2 * ls.cs + idx];
@@ -452,7 +457,7 @@ k_xfwd(const Cx<R>* __restrict__ W, const Cx<R>* __restrict__ twg, Shift sh,
     const int kz = kz0 + l;
     if (kz >= g.h || (!a.full && kz >= g.kzn)) continue;
     const int kx = kval(p, n);
-    const long long io0 = lay_at(a.lo0, p, yi, kz, n);
+    const long long io0 = row_at(a.lo0, p, yi, kz, n);
     const bool ret = active && kz < g.kzn && retained(g, kx, ky, kz);
     if (!ret) {
       // zero outside the retained set only where the output must be complete (full
@@ -461,9 +466,9 @@ k_xfwd(const Cx<R>* __restrict__ W, const Cx<R>* __restrict__ twg, Shift sh,
         for (int c = 0; c < 3; ++c) a.out0[c * a.lo0.cs + io0] = cx(R(0), R(0));
       continue;
     }
-    const long long io1 = lay_at(a.lo1, p, yi, kz, n);
-    const long long ii0 = lay_at(a.li0, p, yi, kz, n);
-    const long long ii1 = lay_at(a.li1, p, yi, kz, n);
+    const long long io1 = row_at(a.lo1, p, yi, kz, n);
+    const long long ii0 = row_at(a.li0, p, yi, kz, n);
+    const long long ii1 = row_at(a.li1, p, yi, kz, n);
     Cx<R> F[3] = {scale(r[0][i], inv_n3), scale(r[1][i], inv_n3), scale(r[2][i], inv_n3)};
     if (sh.on) {
       const Cx<R> phi = cmul(cmul(phx[p], phase1<R>(ky, sh.s[1], n)), phase1<R>(kz, sh.s[2], n));
