@@ -182,8 +182,9 @@ struct XPass : P {
 // with PZA lines per block.  YC: the step sequences run f_xinv<XI, false> and
 // f_ycurl (the vorticity formed in the y-inverse pass, five scratch fields written
 // by the x-inverse passes) instead of f_xinv<XI, true> and f_ypass over six fields.
+// XA: the plan of the adjoint's f_xinv and f_xadj, XL: of its f_xlam.
 template <typename XI, typename YP, typename ZP, int PZ_, typename XF, typename ZA = ZP, int PZA_ = PZ_,
-          bool YC_ = false>
+          bool YC_ = false, typename XA = XF, typename XL = XI>
 struct FastCfg {
   static constexpr int N = XI::N;
   using T = typename XI::T;
@@ -198,6 +199,8 @@ struct FastCfg {
   using Z = ZP;
   using ZAdj = ZA;
   using XFwd = XF;
+  using XAdj = XA;
+  using XLam = XL;
 };
 
 // The padding of a layout's x planes, known to be none at compile time on the grids without
@@ -862,6 +865,12 @@ using LP256b = LinePlan<256, 32, Radices<8, 8, 4>, Radices<4, 8, 8>>;
 // 270 keeps 9 6 5 over 30 threads: 5 6 9 over 54 made the fused pass 154 -> 140, but
 // f_xinv 74 -> 85 and the last stage 121 -> 126.  f_xinv and f_xfwd run one plan, so that
 // chained and single evaluations agree bit for bit.
+// The adjoint's f_xadj holds four line buffers a thread and is left with one tile a CU (144:
+// two) by the plans of more threads at 144, 160 and 192, so the adjoint keeps the y plans
+// there (f_xlam only at 192): f_xadj, us, on the x plans and on the y plans, without and with
+// operands: 144^3 35.8, 50.6 and 19.4, 35.4; 160^3 41.1, 72.2 and 34.6, 64.4; 192^3 61.2, 130
+// and 42.2, 106.  A step adjoint with its first stage kept: 144^3 399 -> 361 us, 160^3 506 -> 485,
+// 192^3 835 -> 784.
 using LP64x = LinePlan<64, 16, Radices<4, 4, 4>, Radices<4, 4, 4>>;
 using Fast64 = FastCfg<LP64x, LP64, LP64, 16, XPass<LP64x, 2>>;
 using LP128x = LinePlan<128, 32, Radices<4, 8, 4>, Radices<4, 8, 4>>;
@@ -869,7 +878,7 @@ using Fast128 = FastCfg<LP128x, LP128b, LP128b, 8, XPass<LP128x, 2>, LP128b, 8, 
 // z and x passes of 192: 6 8 4 over 32 threads, 8 registers a transform (the adjoint z
 // pass and the y passes keep 12 4 4 over 16)
 using LP192z = LinePlan<192, 32, Radices<6, 8, 4>, Radices<4, 8, 6>>;
-using Fast192 = FastCfg<LP192z, LP192, LP192z, 8, XPass<LP192z, 3>, LP192, 8>;
+using Fast192 = FastCfg<LP192z, LP192, LP192z, 8, XPass<LP192z, 3>, LP192, 8, false, LP192, LP192>;
 // z pass of 256: 4 4 4 4 over 64 threads (4 registers a transform, six waves per
 // SIMD; 5% faster than 8 8 4 over 32 at 256^3, whose extra exchange costs more at
 // 128^3); the adjoint z pass keeps 8 8 4 over 32
@@ -930,10 +939,10 @@ using LP270z = LinePlan<270, 32, Radices<10, 3, 9>, Radices<9, 3, 10>>;
 using LP360z = LinePlan<360, 32, Radices<12, 6, 5>, Radices<5, 6, 12>>;
 using LP360za = LinePlan<360, 64, Radices<10, 6, 6>, Radices<6, 6, 10>>;
 using LP144x = LinePlan<144, 24, Radices<6, 6, 4>, Radices<4, 6, 6>>;
-using Fast144 = FastCfg<LP144x, LP144, LP144z, 8, XPass<LP144x, 3>, LP144z, 8, true>;
+using Fast144 = FastCfg<LP144x, LP144, LP144z, 8, XPass<LP144x, 3>, LP144z, 8, true, LP144>;
 using LP160z = LinePlan<160, 32, Radices<4, 8, 5>, Radices<5, 8, 4>>;
 using LP160x = LinePlan<160, 32, Radices<5, 8, 4>, Radices<4, 8, 5>>;
-using Fast160 = FastCfg<LP160x, LP160, LP160z, 8, XPass<LP160x, 3>, LP160, 8>;
+using Fast160 = FastCfg<LP160x, LP160, LP160z, 8, XPass<LP160x, 3>, LP160, 8, false, LP160>;
 using Fast240 = FastCfg<LP240z, LP240, LP240z, 4, XPass<LP240z, 3>>;
 using Fast270 = FastCfg<LP270, LP270, LP270z, 4, LP270, LP270z, 4, true>;
 using LP360x = LinePlan<360, 60, Radices<6, 10, 6>, Radices<6, 10, 6>>;

@@ -99,9 +99,9 @@ ns_status adj_eval_fast(ns_ctx* c, const Cx<typename C::T>* st, ns::Lay lst, con
   constexpr int N = C::N, P = C::PZA;
   const int ntiles = l.ntiles_active;
   if (ntiles > 0) {
-    hipLaunchKernelGGL((ns::f_xinv<typename C::XInv, true>), dim3(ntiles), dim3(C::XInv::L * C::XInv::TPL), 0,
+    hipLaunchKernelGGL((ns::f_xinv<typename C::XAdj, true>), dim3(ntiles), dim3(C::XAdj::L * C::XAdj::TPL), 0,
                        c->stream, st, lst, p.W, p.tw, sh, p.tiles, g);
-    hipLaunchKernelGGL(ns::f_xlam<typename C::XInv>, dim3(ntiles), dim3(C::XInv::L * C::XInv::TPL), 0,
+    hipLaunchKernelGGL(ns::f_xlam<typename C::XLam>, dim3(ntiles), dim3(C::XLam::L * C::XLam::TPL), 0,
                        c->stream, la, p.W, p.tw, sh, p.tiles, g);
     hipLaunchKernelGGL((ns::f_ypass<typename C::Y, +1>), dim3(9 * N * l.ntz), dim3(C::Y::L * C::Y::TPL), 0,
                        c->stream, p.W, p.tw, l.ntz, g);
@@ -113,7 +113,7 @@ ns_status adj_eval_fast(ns_ctx* c, const Cx<typename C::T>* st, ns::Lay lst, con
   aa.ntzf = l.ntzf;
   const int nblk = aa.full ? N * l.ntzf : ntiles;
   if (nblk > 0)
-    hipLaunchKernelGGL((ns::f_xadj<typename C::XFwd, AOP>), dim3(nblk), dim3(C::XFwd::L * C::XFwd::TPL), 0,
+    hipLaunchKernelGGL((ns::f_xadj<typename C::XAdj, AOP>), dim3(nblk), dim3(C::XAdj::L * C::XAdj::TPL), 0,
                        c->stream, p.W, p.tw, sh, p.tiles, g, aa);
   return hip_check(c, hipGetLastError(), "adjoint launch");
 }

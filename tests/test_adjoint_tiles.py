@@ -17,7 +17,7 @@ auto* adjoint = &adj_eval_fast<typename FastOf<{n}>::type, ns::AOP_HEUN>;
 }}
 """
 # size: resident tiles
-TILES = {216: 2, 256: 2}
+TILES = {144: 4, 160: 2, 192: 2, 216: 2, 256: 2}
 
 
 @pytest.mark.parametrize("n,tiles", sorted(TILES.items()))
