@@ -19,19 +19,23 @@
 // conj(c), two transforms with a multiplication by the chirp's transform between them; the
 // DFT of sign - is the conjugate of that of the conjugate.
 //
-// A call is bound by latency: a chain of dependent transforms of 16 to 2048 points on
-// one CU, whose time is that of one wavefront's instructions and LDS round trips.  So a
-// step is one loop over its evaluations with one copy of each transform in the code,
-// plans of 4 to 8 points a thread with every index known at compile time, and lines of
-// up to 256 points inside one wavefront.  Up to 64 points direct sums with every factor
-// in registers are shorter than either (k_direct1d).  Against the kernel before (direct
-// O(n k_max) sums from LDS), 8 signals, one call of one step, launch included: rk4 at n =
-// 22 11.6 -> 9.3 us, 62 24.8 -> 18 us, 128 42.9 -> 10.7 us, 256 84.6 -> 10.2 us, 302 134.7 ->
-// 34.3 us, 1018 891 -> 53 us, 1024 919 -> 18.9 us.  Mixed-radix stages with the plan as an
-// argument took 24.4 us at 256 and 31.8 us at 1024 (index arithmetic on the one chain).
+// A call of few signals is bound by latency: a chain of dependent transforms of 128 to 2048
+// points on one CU, whose time is that of one wavefront's instructions and LDS round trips.
+// So a step is one loop over its evaluations with one copy of each transform in the code,
+// plans of 4 to 8 points a thread with every index known at compile time, and lines of up
+// to 256 points inside one wavefront.  Direct sums are shorter up to 64 points (k_direct1d to
+// 32, with every factor in registers) and for few kept modes (k_sums1d; the rule is at
+// sums_waves).  Against direct O(n k_max) sums from LDS by 256 threads a signal, rk4, one step a
+// call, launch included, us at 8 signals and at 40,000: n = 22 13 -> 9 and 260 -> 82; 48 23 ->
+// 10 and 486 -> 122; 128 51 -> 11 and 1368 -> 183; 256 100 -> 10 and 4250 -> 230; 300 169 -> 35
+// and 7284 -> 3237; 1022 1154 -> 54 and 98,700 -> 8180; 1024 1183 -> 19 and 186,000 -> 1605.
+// Mixed-radix stages with the plan as an argument took 24.4 us at 256 and 31.8 us at 1024
+// (index arithmetic on the one chain).
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "fft_reg.hpp"
 
@@ -222,14 +226,13 @@ __global__ void __launch_bounds__(threads<NF>()) k_model1d(Args a) {
   }
 }
 
-// n <= J (32 or 64): direct sums with every factor in registers.  Thread j of group g
-// (g = 0: unshifted, 1: shifted; both groups keep the state) holds cos and sin of
-// 2 pi j m / n for 1 <= m < n/2, which serve v_j = S_0 + 2 sum_m Re(S_m e^{i ..}) and, m and
-// n - m taken together, F_j = w_0 + (-1)^j w_{n/2} + sum_m ((w_m + w_{n-m}) cos - i (w_m -
-// w_{n-m}) sin); the other operands are LDS broadcasts.
-template <int J>
-__global__ void __launch_bounds__(2 * J) k_direct1d(Args a) {
-  constexpr int M = J / 2;
+// n <= 32: direct sums with every factor in registers.  Thread j of group g (g = 0:
+// unshifted, 1: shifted; both groups keep the state) holds cos and sin of 2 pi j m / n for
+// 1 <= m < n/2, which serve v_j = S_0 + 2 sum_m Re(S_m e^{i ..}) and, m and n - m taken
+// together, F_j = w_0 + (-1)^j w_{n/2} + sum_m ((w_m + w_{n-m}) cos - i (w_m - w_{n-m}) sin);
+// the other operands are LDS broadcasts.
+__global__ void __launch_bounds__(64) k_direct1d(Args a) {
+  constexpr int J = 32, M = J / 2;
   __shared__ C tw[J], xs[2][M + 1], rs[2][J];
   __shared__ double ws[2][J];
   const int j = threadIdx.x % J, g = threadIdx.x / J, n = a.n, half = n / 2;
@@ -307,6 +310,146 @@ __global__ void __launch_bounds__(2 * J) k_direct1d(Args a) {
   if (isk && g == 0) out[j] = s0;
 }
 
+// Few kept modes: direct sums, O(n kmax) instead of O(nf log nf).  Thread t of 64 WAVES keeps
+// mode k = t mod M (M the power of two above kmax; the 64 WAVES / M segments keep the same
+// state).  The points j and n - j share their factors,
+//   v_j, v_{n-j} = S_0 + 2 (sum_m a_m cos -+ sum_m b_m sin),  S_m = a_m + i b_m, at 2 pi j m / n,
+//   F_k = sum_{j <= n/2} (p_j cos - i q_j sin),  p, q = w_j +- w_{n-j} (w_j and 0 at j = 0, n/2):
+// threads along j for v, along k for F, a segment taking every (segments)-th j.  The two
+// shifts of an average share the factors.
+template <int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) k_sums1d(Args a) {
+  constexpr int T = 64 * WAVES;
+  extern __shared__ C lds[];
+  const int t = threadIdx.x, n = a.n, half = n / 2, kmax = a.kmax;
+  C* tw = lds;                  // [n] e^{2 pi i m / n}
+  C* xs = tw + n;               // [2][kmax + 1] the modes, shifted if `on`, and shifted
+  C* pq = xs + 2 * (kmax + 1);  // [2][half + 1] (p_j, q_j)
+  C* part = pq + 2 * (half + 1);  // [2][T] sums of the segments (more than one wavefront)
+  // a quarter of the factors evaluated, the others by symmetry
+  for (int m = t; m <= n / 4; m += T) {
+    const C z = polar_pi(2.0 * (double)m / (double)n);
+    tw[m] = z;
+    tw[half - m] = ns::cx(-z.re, z.im);
+    tw[half + m] = ns::cx(-z.re, -z.im);
+    if (m > 0) tw[n - m] = ns::conj(z);
+  }
+  int M = 2;
+  while (M <= kmax) M *= 2;
+  const int segs = T / M, k = t & (M - 1), seg = t / M;
+  const C* in = reinterpret_cast<const C*>(a.in) + (size_t)blockIdx.x * a.h;
+  C* out = reinterpret_cast<C*>(a.out) + (size_t)blockIdx.x * a.h;
+  const bool kept = k <= kmax;
+  C s0 = kept ? in[k] : ns::cx(0.0, 0.0), cur = s0, sum = ns::cx(0.0, 0.0);
+  const C ph = a.shifted && kept ? polar_pi(2.0 * (double)k * a.shift / (double)n) : ns::cx(1.0, 0.0);
+  const int e0 = seg * k % n, ek = segs * k % n;
+  const double inv_n = 1.0 / (double)n;
+  int step = 0, e = 0;
+  for (;;) {
+    const Eval ev = a.eval[e];
+    if (seg == 0 && kept) {
+      C x = cur;
+      if (k == 0) x.im = 0.0;  // the k = 0 coefficient of a real field is real
+      const C y = ns::cmul(x, ph);
+      xs[k] = ev.on ? y : x;
+      xs[kmax + 1 + k] = y;
+    }
+    ns::exchange_barrier<WAVES == 1>();
+    // v and -v^2 of one signal, or of the two of an average
+    auto points = [&](auto fields) {
+      constexpr int F = decltype(fields)::value;
+      for (int j = t; j <= half; j += T) {
+        double c[F] = {}, d[F] = {};
+        int at = 0;  // (j m) mod n
+#pragma unroll 4
+        for (int m = 1; m <= kmax; ++m) {
+          at += j;
+          if (at >= n) at -= n;
+          const C w = tw[at];
+#pragma unroll
+          for (int f = 0; f < F; ++f) {
+            const C x = xs[f * (kmax + 1) + m];
+            c[f] += x.re * w.re;
+            d[f] += x.im * w.im;
+          }
+        }
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+          const double x0 = xs[f * (kmax + 1)].re;
+          const double u = x0 + 2.0 * (c[f] - d[f]), v = x0 + 2.0 * (c[f] + d[f]);
+          pq[f * (half + 1) + j] =
+              j == 0 || j == half ? ns::cx(-u * u, 0.0) : ns::cx(-u * u - v * v, v * v - u * u);
+        }
+      }
+    };
+    if (ev.pair) points(std::integral_constant<int, 2>());
+    else points(std::integral_constant<int, 1>());
+    ns::exchange_barrier<WAVES == 1>();
+    C r[2] = {ns::cx(0.0, 0.0), ns::cx(0.0, 0.0)};
+    auto modes = [&](auto fields) {
+      constexpr int F = decltype(fields)::value;
+      int at = e0;  // (j k) mod n
+#pragma unroll 4
+      for (int j = seg; j <= half; j += segs) {
+        const C w = tw[at];
+        at += ek;
+        if (at >= n) at -= n;
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+          const C x = pq[f * (half + 1) + j];
+          r[f].re += x.re * w.re;
+          r[f].im -= x.im * w.im;
+        }
+      }
+      for (int off = M; off < 64; off *= 2) {
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+          r[f].re += __shfl_xor(r[f].re, off);
+          r[f].im += __shfl_xor(r[f].im, off);
+        }
+      }
+      if constexpr (WAVES > 1) {  // in one order for every segment: they keep the same state
+        const int period = M > 64 ? M : 64;
+#pragma unroll
+        for (int f = 0; f < F; ++f) part[f * T + t] = r[f];
+        __syncthreads();
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+          r[f] = part[f * T + (t & (period - 1))];
+          for (int q = period + (t & (period - 1)); q < T; q += period) r[f] = r[f] + part[f * T + q];
+        }
+      }
+    };
+    if (ev.pair) modes(std::integral_constant<int, 2>());
+    else modes(std::integral_constant<int, 1>());
+    C g = ns::cx(0.0, 0.0);
+    if (kept) {
+      g = ns::scale(ev.on ? ns::cmulc(r[0], ph) : r[0], inv_n);
+      if (ev.pair) g = ns::scale(g + ns::scale(ns::cmulc(r[1], ph), inv_n), 0.5);
+      if (k == 0) g.im = 0.0;  // the mean of a real field
+    }
+    sum = ev.b == 0.0 ? ns::cx(0.0, 0.0) : sum + ns::scale(g, ev.b);
+    if (e + 1 < a.nevals) {
+      cur = s0 + ns::scale(g, ev.c);
+    } else {
+      cur = s0 = a.nsteps > 0 ? s0 + ns::scale(sum, a.fin) : g;
+      sum = ns::cx(0.0, 0.0);
+    }
+    if (++e == a.nevals) {
+      if (++step >= a.nsteps) break;
+      e = 0;
+    }
+  }
+  if (seg == 0 && kept) out[k] = s0;
+  for (int m = kmax + 1 + t; m < a.h; m += T) out[m] = a.nsteps > 0 ? in[m] : ns::cx(0.0, 0.0);
+}
+
+template <int WAVES>
+void launch_sums(const Args& a, int batch, hipStream_t stream) {
+  const size_t entries = (size_t)a.n + 2 * (a.kmax + 1) + 2 * (a.n / 2 + 1) + (WAVES > 1 ? 128 * WAVES : 0);
+  hipLaunchKernelGGL(k_sums1d<WAVES>, dim3((unsigned)batch), dim3(64 * WAVES), entries * sizeof(C), stream, a);
+}
+
 // FFT length of signals of n > 64 points.
 inline int fft_length(int n) {
   int nf = 128;
@@ -314,6 +457,37 @@ inline int fft_length(int n) {
   if (nf == n) return nf;
   while (nf < 2 * n - 1) nf *= 2;
   return nf;
+}
+
+// Terms a thread of k_sums1d<waves> adds up in an evaluation.
+inline int sums_terms(int n, int kmax, int waves) {
+  const int points = n / 2 + 1, threads = 64 * waves;
+  int m = 2;
+  while (m <= kmax) m *= 2;
+  return (points + threads - 1) / threads * kmax + (points * m + threads - 1) / threads;
+}
+
+// Wavefronts a signal of k_sums1d, or 0 where the transforms are better: by the terms a
+// thread adds up against the transforms' length, from the length and the kept modes alone,
+// so that a signal's result does not depend on its batch.  An average of two shifts costs
+// the transforms one evaluation and the sums nearly two, so it has limits of its own.
+// Measured on both sides of the lines, us a call, transforms / sums, one signal and 40,000
+// signals, classical rk4 and (in brackets) ps_exact:
+//   one wavefront: n = 126, 31 modes, 63 terms 15 / 14 and 468 / 262 (10 / 12, 269 / 178), 41
+//     modes, 105 terms 15 / 18 and 469 / 420; n = 90, 29 modes, 52 terms 16 / 12, 470 / 201 (11 /
+//     10, 270 / 143)
+//   four, 512 points: n = 130, 64 modes, 97 terms 23 / 18, 1255 / 1003 (15 / 15, 704 / 703);
+//     n = 200, 66 modes, 117 terms 24 / 22, 1252 / 1445
+//   1024: n = 450, 74 modes, 187 terms 35 / 31, 3250 / 3137 (21 / 29), 112 modes, 225 terms 34 /
+//     36, 3257 / 3750; n = 384, 63 modes, 112 terms (20 / 19, 1781 / 1100)
+//   2048: n = 600, 98 modes, 347 terms 52 / 53, 7968 / 4933 (31 / 47); 59 modes, 194 terms (30 /
+//     29, 4622 / 1739); n = 720, 118 modes, 417 terms 52 / 64
+inline int sums_waves(int n, int kmax, bool pair) {
+  const int nf = fft_length(n);
+  if (n > 64 && nf == n) return 0;
+  if (kmax < 64 && sums_terms(n, kmax, 1) <= (pair ? 54 : 70)) return 1;
+  const int most = nf == 2048 ? (pair ? 200 : 350) : nf == 1024 ? (pair ? 115 : 190) : nf == 512 ? (pair ? 95 : 100) : 0;
+  return kmax < 256 && sums_terms(n, kmax, 4) <= most ? 4 : 0;
 }
 
 // The evaluations of a scheme's step (classical Runge-Kutta forms; there is no linear
@@ -366,12 +540,15 @@ void launch_nf(const Args& a, int batch, hipStream_t stream) {
 
 inline void launch(const Args& a, int batch, hipStream_t stream) {
   if (a.n <= 32) {
-    hipLaunchKernelGGL(k_direct1d<32>, dim3((unsigned)batch), dim3(64), 0, stream, a);
+    hipLaunchKernelGGL(k_direct1d, dim3((unsigned)batch), dim3(64), 0, stream, a);
     return;
   }
-  if (a.n <= 64) {
-    hipLaunchKernelGGL(k_direct1d<64>, dim3((unsigned)batch), dim3(128), 0, stream, a);
-    return;
+  bool pair = false;
+  for (int e = 0; e < a.nevals; ++e) pair = pair || a.eval[e].pair != 0;
+  switch (sums_waves(a.n, a.kmax, pair)) {
+    case 1: launch_sums<1>(a, batch, stream); return;
+    case 4: launch_sums<4>(a, batch, stream); return;
+    default: break;
   }
   switch (fft_length(a.n)) {
     case 128: launch_nf<128>(a, batch, stream); break;
