@@ -184,7 +184,7 @@ struct XPass : P {
 // by the x-inverse passes) instead of f_xinv<XI, true> and f_ypass over six fields.
 // XA: the plan of the adjoint's f_xinv and f_xadj, XL: of its f_xlam.
 template <typename XI, typename YP, typename ZP, int PZ_, typename XF, typename ZA = ZP, int PZA_ = PZ_,
-          bool YC_ = false, typename XA = XF, typename XL = XI>
+          typename XA = XF, typename XL = XI, bool YC_ = false>
 struct FastCfg {
   static constexpr int N = XI::N;
   using T = typename XI::T;
@@ -874,16 +874,16 @@ using LP256b = LinePlan<256, 32, Radices<8, 8, 4>, Radices<4, 8, 8>>;
 using LP64x = LinePlan<64, 16, Radices<4, 4, 4>, Radices<4, 4, 4>>;
 using Fast64 = FastCfg<LP64x, LP64, LP64, 16, XPass<LP64x, 2>>;
 using LP128x = LinePlan<128, 32, Radices<4, 8, 4>, Radices<4, 8, 4>>;
-using Fast128 = FastCfg<LP128x, LP128b, LP128b, 8, XPass<LP128x, 2>, LP128b, 8, true>;
+using Fast128 = FastCfg<LP128x, LP128b, LP128b, 8, XPass<LP128x, 2>, LP128b, 8, XPass<LP128x, 2>, LP128x, true>;
 // z and x passes of 192: 6 8 4 over 32 threads, 8 registers a transform (the adjoint z
 // pass and the y passes keep 12 4 4 over 16)
 using LP192z = LinePlan<192, 32, Radices<6, 8, 4>, Radices<4, 8, 6>>;
-using Fast192 = FastCfg<LP192z, LP192, LP192z, 8, XPass<LP192z, 3>, LP192, 8, false, LP192, LP192>;
+using Fast192 = FastCfg<LP192z, LP192, LP192z, 8, XPass<LP192z, 3>, LP192, 8, LP192, LP192>;
 // z pass of 256: 4 4 4 4 over 64 threads (4 registers a transform, six waves per
 // SIMD; 5% faster than 8 8 4 over 32 at 256^3, whose extra exchange costs more at
 // 128^3); the adjoint z pass keeps 8 8 4 over 32
 using LP256z = LinePlan<256, 64, Radices<4, 4, 4, 4>, Radices<4, 4, 4, 4>>;
-using Fast256 = FastCfg<LP256b, LP256b, LP256z, 4, LP256b, LP256b, 8, true>;
+using Fast256 = FastCfg<LP256b, LP256b, LP256z, 4, LP256b, LP256b, 8, LP256b, LP256b, true>;
 // 216 = 12 6 3 and 324 = 12 3 3 3 with 12 points per thread (18 and 27 threads per
 // line), the y passes: the grids of the k_max = 108 comparison
 using LP216 = LinePlan<216, 18, Radices<12, 6, 3>, Radices<3, 6, 12>>;
@@ -939,12 +939,12 @@ using LP270z = LinePlan<270, 32, Radices<10, 3, 9>, Radices<9, 3, 10>>;
 using LP360z = LinePlan<360, 32, Radices<12, 6, 5>, Radices<5, 6, 12>>;
 using LP360za = LinePlan<360, 64, Radices<10, 6, 6>, Radices<6, 6, 10>>;
 using LP144x = LinePlan<144, 24, Radices<6, 6, 4>, Radices<4, 6, 6>>;
-using Fast144 = FastCfg<LP144x, LP144, LP144z, 8, XPass<LP144x, 3>, LP144z, 8, true, LP144>;
+using Fast144 = FastCfg<LP144x, LP144, LP144z, 8, XPass<LP144x, 3>, LP144z, 8, LP144, LP144x, true>;
 using LP160z = LinePlan<160, 32, Radices<4, 8, 5>, Radices<5, 8, 4>>;
 using LP160x = LinePlan<160, 32, Radices<5, 8, 4>, Radices<4, 8, 5>>;
-using Fast160 = FastCfg<LP160x, LP160, LP160z, 8, XPass<LP160x, 3>, LP160, 8, false, LP160>;
+using Fast160 = FastCfg<LP160x, LP160, LP160z, 8, XPass<LP160x, 3>, LP160, 8, LP160>;
 using Fast240 = FastCfg<LP240z, LP240, LP240z, 4, XPass<LP240z, 3>>;
-using Fast270 = FastCfg<LP270, LP270, LP270z, 4, LP270, LP270z, 4, true>;
+using Fast270 = FastCfg<LP270, LP270, LP270z, 4, LP270, LP270z, 4, LP270, LP270, true>;
 using LP360x = LinePlan<360, 60, Radices<6, 10, 6>, Radices<6, 10, 6>>;
 using Fast360 = FastCfg<LP360x, LP360, LP360z, 4, XPass<LP360x, 6>, LP360za, 4>;
 
