@@ -9,19 +9,10 @@
 namespace nsh {
 
 template <int N> struct FastOf;
-template <> struct FastOf<64> { using type = ns::Fast64; };
-template <> struct FastOf<128> { using type = ns::Fast128; };
-template <> struct FastOf<192> { using type = ns::Fast192; };
-template <> struct FastOf<216> { using type = ns::Fast216; };
-template <> struct FastOf<256> { using type = ns::Fast256; };
-template <> struct FastOf<324> { using type = ns::Fast324; };
-template <> struct FastOf<384> { using type = ns::Fast384; };
-template <> struct FastOf<512> { using type = ns::Fast512; };
-template <> struct FastOf<144> { using type = ns::Fast144; };
-template <> struct FastOf<160> { using type = ns::Fast160; };
-template <> struct FastOf<240> { using type = ns::Fast240; };
-template <> struct FastOf<270> { using type = ns::Fast270; };
-template <> struct FastOf<360> { using type = ns::Fast360; };
+#define NS_FAST_OF(N) \
+  template <> struct FastOf<N> { using type = ns::Fast##N; };
+NS_FOR_EACH_STAGE_SIZE(NS_FAST_OF)
+#undef NS_FAST_OF
 
 // Specialised passes for one compile-time size (same semantics and layout).
 template <typename C, int OP, int FEED>

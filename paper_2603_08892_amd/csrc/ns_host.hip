@@ -112,8 +112,11 @@ const SizePasses<R>* sized_passes(int n) {
 
 // Sizes with FP32 passes specialised per stage (ns_fast.hpp).
 bool stage_size(int n) {
-  return n == 64 || n == 128 || n == 144 || n == 160 || n == 192 || n == 216 || n == 240 || n == 256 || n == 270 ||
-         n == 324 || n == 360 || n == 384 || n == 512;
+#define NS_STAGE_CASE(N) \
+  if (n == N) return true;
+  NS_FOR_EACH_STAGE_SIZE(NS_STAGE_CASE)
+#undef NS_STAGE_CASE
+  return false;
 }
 
 // Whether the config runs specialised passes (unless it asks for the size-generic ones).
@@ -245,22 +248,10 @@ ns_status eval(ns_ctx* c, const Cx<R>* in, ns::Lay lin, const double* s, EpiArgs
   const ns::Shift sh = make_shift(s);
   hipError_t e;
   if constexpr (std::is_same<R, float>::value) {
-    switch (c->fast) {
-      case 64: return fast_eval<64, OP>(c, in, lin, sh, a, ch);
-      case 128: return fast_eval<128, OP>(c, in, lin, sh, a, ch);
-      case 144: return fast_eval<144, OP>(c, in, lin, sh, a, ch);
-      case 160: return fast_eval<160, OP>(c, in, lin, sh, a, ch);
-      case 192: return fast_eval<192, OP>(c, in, lin, sh, a, ch);
-      case 216: return fast_eval<216, OP>(c, in, lin, sh, a, ch);
-      case 240: return fast_eval<240, OP>(c, in, lin, sh, a, ch);
-      case 256: return fast_eval<256, OP>(c, in, lin, sh, a, ch);
-      case 270: return fast_eval<270, OP>(c, in, lin, sh, a, ch);
-      case 324: return fast_eval<324, OP>(c, in, lin, sh, a, ch);
-      case 360: return fast_eval<360, OP>(c, in, lin, sh, a, ch);
-      case 384: return fast_eval<384, OP>(c, in, lin, sh, a, ch);
-      case 512: return fast_eval<512, OP>(c, in, lin, sh, a, ch);
-      default: break;
-    }
+#define NS_STAGE_CASE(N) \
+    if (c->fast == N) return fast_eval<N, OP>(c, in, lin, sh, a, ch);
+    NS_FOR_EACH_STAGE_SIZE(NS_STAGE_CASE)
+#undef NS_STAGE_CASE
   }
   if (const SizePasses<R>* z = sized<R>(c)) return z->eval(c, OP, in, lin, sh, a, ch);
   if (ch) ch->fused = false;  // the size-generic passes run every x-inverse pass on its own
@@ -599,22 +590,10 @@ ns_status adj_eval(ns_ctx* c, const Cx<R>* st, ns::Lay lst, const double* s, con
   const ns::Shift sh = make_shift(s);
   hipError_t e;
   if constexpr (std::is_same<R, float>::value) {
-    switch (c->fast) {
-      case 64: return fast_adj_eval<64, AOP>(c, st, lst, sh, la, aa);
-      case 128: return fast_adj_eval<128, AOP>(c, st, lst, sh, la, aa);
-      case 144: return fast_adj_eval<144, AOP>(c, st, lst, sh, la, aa);
-      case 160: return fast_adj_eval<160, AOP>(c, st, lst, sh, la, aa);
-      case 192: return fast_adj_eval<192, AOP>(c, st, lst, sh, la, aa);
-      case 216: return fast_adj_eval<216, AOP>(c, st, lst, sh, la, aa);
-      case 240: return fast_adj_eval<240, AOP>(c, st, lst, sh, la, aa);
-      case 256: return fast_adj_eval<256, AOP>(c, st, lst, sh, la, aa);
-      case 270: return fast_adj_eval<270, AOP>(c, st, lst, sh, la, aa);
-      case 324: return fast_adj_eval<324, AOP>(c, st, lst, sh, la, aa);
-      case 360: return fast_adj_eval<360, AOP>(c, st, lst, sh, la, aa);
-      case 384: return fast_adj_eval<384, AOP>(c, st, lst, sh, la, aa);
-      case 512: return fast_adj_eval<512, AOP>(c, st, lst, sh, la, aa);
-      default: break;
-    }
+#define NS_STAGE_CASE(N) \
+    if (c->fast == N) return fast_adj_eval<N, AOP>(c, st, lst, sh, la, aa);
+    NS_FOR_EACH_STAGE_SIZE(NS_STAGE_CASE)
+#undef NS_STAGE_CASE
   }
   if (const SizePasses<R>* z = sized<R>(c)) return z->adj(c, AOP, st, lst, sh, la, aa);
   const size_t lds = lds_strided(l);

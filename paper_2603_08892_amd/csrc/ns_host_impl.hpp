@@ -219,6 +219,12 @@ inline hipError_t launch_xfwd(ns_ctx* c, const Ptrs<R>& p, const ns::Shift& sh, 
   return hipGetLastError();
 }
 
+// The sizes with FP32 passes specialised per stage, one unit fast_<N>.hip each.  The one list of
+// them: a context of such a size runs them in every evaluation (the size-generic passes
+// know nothing of the padding of its planes).
+#define NS_FOR_EACH_STAGE_SIZE(X) \
+  X(64) X(128) X(144) X(160) X(192) X(216) X(240) X(256) X(270) X(324) X(360) X(384) X(512)
+
 // Specialised FP32 passes of size N (defined and instantiated for every op in the
 // translation unit of that size): one evaluation of the nonlinear term, and one
 // transposed evaluation.
