@@ -1,5 +1,5 @@
-// ns_fast_adjoint.hpp -- specialised FP32 passes of the transposed linearised
-// nonlinear term (gfx950), for the sizes of ns_fast.hpp.  Same operations and
+// ns_fast_adjoint.hpp -- specialised passes of the transposed linearised nonlinear term
+// (gfx950), for the sizes and types of ns_fast.hpp.  Same operations and
 // scratch fields as the size-generic kernels of ns_adjoint.hpp:
 //   M conj(phi) [ FFT(omega x lt) + i k x FFT(lt x u) ],
 //   u = IFFT(phi M a), omega = IFFT(i k x phi M a), lt = IFFT(phi P M lam);
@@ -89,8 +89,7 @@ f_xlam(LamArgs<typename C::T> la, Cx<typename C::T>* __restrict__ W, const Cx<ty
 }
 
 // ------------------------------------------------------------------ z pass
-// P lines per block, TPL threads per line (block barriers when a line straddles
-// wavefronts).  Inverse slices
+// P lines per block, TPL threads per line, a line inside one wavefront.  Inverse slices
 // (u_x + i u_y), (u_z + i w_x), (w_y + i w_z), (l_x + i l_y), (l_z + i 0) from the
 // half spectra of fields 0..8; the products g1 = omega x lt and g2 = lt x u stay
 // in registers; forward slices (g1x + i g1y), (g1z + i g2x), (g2y + i g2z), each
@@ -103,7 +102,7 @@ f_zadj(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
   using FI = RegFft<N, TPL, +1, typename C::Inv>;
   using FF = RegFft<N, TPL, -1, typename C::Fwd>;
   static_assert(FI::RL == FF::R0, "the forward transform must start with the last inverse radix");
-  constexpr bool WV = (64 % TPL == 0);  // else a line straddles wavefronts: block barriers
+  static_assert(64 % TPL == 0, "a line inside one wavefront");
   constexpr int LP = line_pitch(N);
   __shared__ Cx<T> tw[N];
   __shared__ Cx<T> xb[P * LP];  // exchanges
@@ -128,7 +127,7 @@ f_zadj(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
       else if (pos < HN) v[i] = cx(a.re - bb.im, a.im + bb.re);
       else v[i] = cx(a.re + bb.im, bb.re - a.im);
     }
-    FI::template run<WV>(v, t, lv, tw);
+    FI::template run<true>(v, t, lv, tw);
     if (q < 4) {
 #pragma unroll
       for (int i = 0; i < EPT; ++i) z[q][i] = v[i];
@@ -154,12 +153,12 @@ f_zadj(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
       const T im = q == 0 ? g1[1][i] : (q == 1 ? g2[0][i] : g2[2][i]);
       v[i] = cx(re, im);
     }
-    FF::template run<WV>(v, t, lv, tw);
-    exchange_barrier<WV>();  // the previous slice's split has read sp
+    FF::template run<true>(v, t, lv, tw);
+    exchange_barrier<true>();  // the previous slice's split has read sp
 #pragma unroll
     for (int i = 0; i < EPT; ++i)
       if (FF::out_ok(t, i)) sp[p * N + FF::out_pos(t, i)] = v[i];
-    exchange_barrier<WV>();
+    exchange_barrier<true>();
     for (int k = t; k < g.kzn; k += TPL) {
       const Cx<T> c1 = sp[p * N + k], c2 = sp[p * N + ((N - k) % N)];
       const uint32_t off = lbase + k;
