@@ -297,7 +297,7 @@ ns_status ns_budget_read(ns_ctx* ctx, double* out);
  * 3 y-forward, 4 x-forward (projection, mask, Runge-Kutta stage), 5 x-forward
  * that also runs the next evaluation's x-inverse pass on the stage output it
  * computes (the step sequences chain their evaluations this way with the
- * specialised FP32 passes).
+ * specialised passes).
  * ns_timing_read waits for the stream, writes per pass the summed event-to-event
  * milliseconds and the number of launches since the previous read (host arrays
  * of NS_NUM_PASSES entries; either may be NULL) and clears the record. */

@@ -42,8 +42,9 @@ __device__ __forceinline__ int shell_small(int k2) {
 // us, 256^3 FP64 261 -> 195 us; a plain copy reaches 4.9 to 6 TB/s.  Up to 96^3 a call is its
 // launches and the wait, about 40 us either way.
 //
-// Threads of a block at most: two fields of FP64 (96 loads of 16 bytes a lane) take more
-// than the 128 registers a block of 1024 threads leaves.
+// Threads of a block at most: the four rows of two FP64 fields that a lane loads together (24
+// loads of 16 bytes, 96 registers) and what it works with take more than the 128 registers a
+// block of 1024 threads leaves.
 template <typename R, bool NH>
 constexpr int spectra_threads() { return NH && sizeof(R) == 8 ? 512 : 1024; }
 template <typename R, bool NH>

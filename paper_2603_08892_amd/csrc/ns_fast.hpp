@@ -681,107 +681,107 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
   if (FEED == 0 && !epi_on) return;
   const T inv_n3 = T(1) / (T(N) * T(N) * T(N));
   if (epi_on) {
-  if (!active) load_ops(0);
+    if (!active) load_ops(0);
 #pragma unroll
-  for (int c0 = 0; c0 < EPT; c0 += CH) {
-  if (c0 + CH < EPT) load_ops(c0 + CH);
+    for (int c0 = 0; c0 < EPT; c0 += CH) {
+      if (c0 + CH < EPT) load_ops(c0 + CH);
 #pragma unroll
-  for (int j = 0; j < CH; ++j) {
-    const int i = c0 + j;
-    if (i >= EPT) break;
-    if (!F::out_ok(t, i)) continue;  // no point in this register
-    const int p = F::out_pos(t, i);
-    const int kx = kval(p, N);
-    const uint32_t io0 = (uint32_t)((p * N + yi) * a.lo0.pitch + p * pad_of<C>(a.lo0.pad) + kz);
-    if (!(line_kept && keep(kx))) {
-      // outside the retained set: zero in outputs that must be complete (full
-      // mode, the caller's arrays); stage buffers are only read at retained modes
-      if (a.full)
-        for (int c = 0; c < 3; ++c) st_off(a.out0 + c * a.lo0.cs, io0, cx(T(0), T(0)));
-      continue;
-    }
-    const uint32_t io1 = use1 ? (uint32_t)((p * N + yi) * a.lo1.pitch + p * pad_of<C>(a.lo1.pad) + kz) : 0u;
-    Cx<T> Fv[3] = {scale(r[0][i], inv_n3), scale(r[1][i], inv_n3), scale(r[2][i], inv_n3)};
-    if (sh.on) {
-      const Cx<T> phi = cmul(phx[p], phyz);
-      Fv[0] = cmulc(Fv[0], phi);
-      Fv[1] = cmulc(Fv[1], phi);
-      Fv[2] = cmulc(Fv[2], phi);
-    }
-    const int k2 = kx * kx + ky * ky + kz * kz;
-    if (k2 == 0) {
-      Fv[0] = Fv[1] = Fv[2] = cx(T(0), T(0));
-    } else {
-      const T rk2 = T(1) / T(k2);
-      const T kxr = T(kx), kyr = T(ky), kzr = T(kz);
-      const Cx<T> kd = scale(scale(Fv[0], kxr) + scale(Fv[1], kyr) + scale(Fv[2], kzr), rk2);
-      Fv[0] = Fv[0] - scale(kd, kxr);
-      Fv[1] = Fv[1] - scale(kd, kyr);
-      Fv[2] = Fv[2] - scale(kd, kzr);
-    }
-    T eh = T(1), edt = T(1);
-    if (op_uses_etab(op)) { eh = a.eh[k2]; edt = a.edt[k2]; }
-    const T dt = a.dt;
+      for (int j = 0; j < CH; ++j) {
+        const int i = c0 + j;
+        if (i >= EPT) break;
+        if (!F::out_ok(t, i)) continue;  // no point in this register
+        const int p = F::out_pos(t, i);
+        const int kx = kval(p, N);
+        const uint32_t io0 = (uint32_t)((p * N + yi) * a.lo0.pitch + p * pad_of<C>(a.lo0.pad) + kz);
+        if (!(line_kept && keep(kx))) {
+          // outside the retained set: zero in outputs that must be complete (full
+          // mode, the caller's arrays); stage buffers are only read at retained modes
+          if (a.full)
+            for (int c = 0; c < 3; ++c) st_off(a.out0 + c * a.lo0.cs, io0, cx(T(0), T(0)));
+          continue;
+        }
+        const uint32_t io1 = use1 ? (uint32_t)((p * N + yi) * a.lo1.pitch + p * pad_of<C>(a.lo1.pad) + kz) : 0u;
+        Cx<T> Fv[3] = {scale(r[0][i], inv_n3), scale(r[1][i], inv_n3), scale(r[2][i], inv_n3)};
+        if (sh.on) {
+          const Cx<T> phi = cmul(phx[p], phyz);
+          Fv[0] = cmulc(Fv[0], phi);
+          Fv[1] = cmulc(Fv[1], phi);
+          Fv[2] = cmulc(Fv[2], phi);
+        }
+        const int k2 = kx * kx + ky * ky + kz * kz;
+        if (k2 == 0) {
+          Fv[0] = Fv[1] = Fv[2] = cx(T(0), T(0));
+        } else {
+          const T rk2 = T(1) / T(k2);
+          const T kxr = T(kx), kyr = T(ky), kzr = T(kz);
+          const Cx<T> kd = scale(scale(Fv[0], kxr) + scale(Fv[1], kyr) + scale(Fv[2], kzr), rk2);
+          Fv[0] = Fv[0] - scale(kd, kxr);
+          Fv[1] = Fv[1] - scale(kd, kyr);
+          Fv[2] = Fv[2] - scale(kd, kzr);
+        }
+        T eh = T(1), edt = T(1);
+        if (op_uses_etab(op)) { eh = a.eh[k2]; edt = a.edt[k2]; }
+        const T dt = a.dt;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      Cx<T>* out0 = a.out0 + c * a.lo0.cs;
-      Cx<T>* out1 = use1 ? a.out1 + c * a.lo1.cs : nullptr;
-      Cx<T> Nv = Fv[c];
-      Cx<T> O = cx(T(0), T(0));
-      if (op_forced(op) && a.force != nullptr && k2 >= 4 && k2 <= 9)
-        O = a.force[c * 196 + ((kx + 3) * 7 + (ky + 3)) * 4 + kz];
-      if (op != OP_HEUN1) Nv = Nv + O;  // RK4 slopes N + O (zero for the other ops)
-      Cx<T> s0 = cx(T(0), T(0)), s1 = cx(T(0), T(0));
-      if constexpr (may0) s0 = s0v[(c0 / CH) % NBUF][c][j];
-      if constexpr (may1) s1 = s1v[(c0 / CH) % NBUF][c][j];
-      Cx<T> v0 = cx(T(0), T(0)), v1 = cx(T(0), T(0));
-      if (op == OP_STORE) {
-        v0 = Nv;
-      } else if (op == OP_AVG) {
-        v0 = scale(s1 + Nv, T(0.5));
-      } else if (op == OP_HEUN1) {
-        v1 = scale(s0 + scale(Nv + O, dt), edt);
-        v0 = scale(s0, edt) + scale(Nv + O + O, T(0.5) * dt * eh);
-      } else if (op == OP_HEUN2) {
-        v0 = s1 + scale(Nv, T(0.5) * dt * eh);
-      } else if (op == OP_EX1B) {
-        v0 = scale(s0 + scale(s1 + Nv, T(0.5) * dt * a.w), eh);
-      } else if (op == OP_EX2B) {
-        v0 = scale(s0, edt) + scale(s1 + Nv, dt * a.w * eh);
-      } else if (op == OP_RK4_0) {
-        v1 = scale(s0 + scale(Nv, T(0.5) * dt), eh);
-        v0 = scale(s0 + scale(Nv, dt / T(6)), edt);
-      } else if (op == OP_RK4_1) {
-        v1 = scale(s0, eh) + scale(Nv, T(0.5) * dt);
-        v0 = s1 + scale(Nv, dt / T(3) * eh);
-      } else if (op == OP_RK4_2) {
-        v1 = scale(s0, edt) + scale(Nv, dt * eh);
-        v0 = s1 + scale(Nv, dt / T(3) * eh);
-      } else if (op == OP_RK4_3) {
-        v0 = s1 + scale(Nv, dt / T(6));
-      } else if (op == OP_ACC) {
-        v0 = s1 + Nv;
-      } else if (op == OP_MID1) {
-        v0 = scale(s0 + scale(Nv, T(0.5) * dt), eh);
-      } else if (op == OP_MID2) {
-        v0 = scale(s0, edt) + scale(Nv, dt * eh);
-      } else if (op == OP_EUL) {
-        v0 = scale(s0 + scale(Nv, dt), edt);
-      } else {  // OP_EULAV
-        v0 = scale(s0 + scale(s1 + Nv, dt * a.w), edt);
-      }
-      if constexpr (may_out1) {
-        if (use1) {
-          if (st1) st_off<true>(out1, io1, v1);
-          else st_off(out1, io1, v1);
+        for (int c = 0; c < 3; ++c) {
+          Cx<T>* out0 = a.out0 + c * a.lo0.cs;
+          Cx<T>* out1 = use1 ? a.out1 + c * a.lo1.cs : nullptr;
+          Cx<T> Nv = Fv[c];
+          Cx<T> O = cx(T(0), T(0));
+          if (op_forced(op) && a.force != nullptr && k2 >= 4 && k2 <= 9)
+            O = a.force[c * 196 + ((kx + 3) * 7 + (ky + 3)) * 4 + kz];
+          if (op != OP_HEUN1) Nv = Nv + O;  // RK4 slopes N + O (zero for the other ops)
+          Cx<T> s0 = cx(T(0), T(0)), s1 = cx(T(0), T(0));
+          if constexpr (may0) s0 = s0v[(c0 / CH) % NBUF][c][j];
+          if constexpr (may1) s1 = s1v[(c0 / CH) % NBUF][c][j];
+          Cx<T> v0 = cx(T(0), T(0)), v1 = cx(T(0), T(0));
+          if (op == OP_STORE) {
+            v0 = Nv;
+          } else if (op == OP_AVG) {
+            v0 = scale(s1 + Nv, T(0.5));
+          } else if (op == OP_HEUN1) {
+            v1 = scale(s0 + scale(Nv + O, dt), edt);
+            v0 = scale(s0, edt) + scale(Nv + O + O, T(0.5) * dt * eh);
+          } else if (op == OP_HEUN2) {
+            v0 = s1 + scale(Nv, T(0.5) * dt * eh);
+          } else if (op == OP_EX1B) {
+            v0 = scale(s0 + scale(s1 + Nv, T(0.5) * dt * a.w), eh);
+          } else if (op == OP_EX2B) {
+            v0 = scale(s0, edt) + scale(s1 + Nv, dt * a.w * eh);
+          } else if (op == OP_RK4_0) {
+            v1 = scale(s0 + scale(Nv, T(0.5) * dt), eh);
+            v0 = scale(s0 + scale(Nv, dt / T(6)), edt);
+          } else if (op == OP_RK4_1) {
+            v1 = scale(s0, eh) + scale(Nv, T(0.5) * dt);
+            v0 = s1 + scale(Nv, dt / T(3) * eh);
+          } else if (op == OP_RK4_2) {
+            v1 = scale(s0, edt) + scale(Nv, dt * eh);
+            v0 = s1 + scale(Nv, dt / T(3) * eh);
+          } else if (op == OP_RK4_3) {
+            v0 = s1 + scale(Nv, dt / T(6));
+          } else if (op == OP_ACC) {
+            v0 = s1 + Nv;
+          } else if (op == OP_MID1) {
+            v0 = scale(s0 + scale(Nv, T(0.5) * dt), eh);
+          } else if (op == OP_MID2) {
+            v0 = scale(s0, edt) + scale(Nv, dt * eh);
+          } else if (op == OP_EUL) {
+            v0 = scale(s0 + scale(Nv, dt), edt);
+          } else {  // OP_EULAV
+            v0 = scale(s0 + scale(s1 + Nv, dt * a.w), edt);
+          }
+          if constexpr (may_out1) {
+            if (use1) {
+              if (st1) st_off<true>(out1, io1, v1);
+              else st_off(out1, io1, v1);
+            }
+          }
+          if (st0) st_off<true>(out0, io0, v0);
+          else st_off(out0, io0, v0);
+          if constexpr (FEED != 0) nx[c][i] = feed == 1 ? v0 : v1;
         }
       }
-      if (st0) st_off<true>(out0, io0, v0);
-      else st_off(out0, io0, v0);
-      if constexpr (FEED != 0) nx[c][i] = feed == 1 ? v0 : v1;
     }
-  }
-  }
   }
   if constexpr (FEED != 0) {
     // the next evaluation's x-inverse pass on this tile (as f_xinv<C, CURL>, from registers)
@@ -912,8 +912,9 @@ using Fast384 = FastCfg<LP384x, LP384, LP384z, 4, LP384x, LP384, 4>;
 // with one wavefront per line, four lines per z block (at eight, one 512-thread
 // block of about 130 registers a thread is all a CU holds); x passes 16 8 4 with
 // 32 threads per line, so that a 16-column tile is a 512-thread block of up to 256
-// registers a thread (the chained x pass still spills some, but fewer waves per
-// line and more registers measured faster than 1024-thread tiles of 128)
+// registers a thread (of the chained passes only the two middle RK4 stages spill, three
+// registers; fewer waves per line and more registers measured faster than 1024-thread
+// tiles of 128)
 using LP512 = LinePlan<512, 64, Radices<8, 8, 8>, Radices<8, 8, 8>>;
 using LP512x = LinePlan<512, 32, Radices<16, 8, 4>, Radices<4, 8, 16>>;
 using Fast512 = FastCfg<LP512x, LP512, LP512, 4, XPass<LP512x, 4>>;

@@ -26,9 +26,10 @@
 // to 256 points inside one wavefront.  Direct sums are shorter up to 64 points (k_direct1d to
 // 32, with every factor in registers) and for few kept modes (k_sums1d; the rule is at
 // sums_waves).  Against direct O(n k_max) sums from LDS by 256 threads a signal, rk4, one step a
-// call, launch included, us at 8 signals and at 40,000: n = 22 13 -> 9 and 260 -> 82; 48 23 ->
-// 10 and 486 -> 122; 128 51 -> 11 and 1368 -> 183; 256 100 -> 10 and 4250 -> 230; 300 169 -> 35
-// and 7284 -> 3237; 1022 1154 -> 54 and 98,700 -> 8180; 1024 1183 -> 19 and 186,000 -> 1605.
+// call, launch included, us at 8 signals and at 40,000: n = 22 13 -> 8 and 260 -> 78; 48 23 -> 11
+// and 484 -> 121; 128 51 -> 11 and 1363 -> 183; 256 101 -> 10 and 4379 -> 234; 258 with 6 modes 65
+// -> 13 and 1394 -> 176; 300 169 -> 35 and 7317 -> 3235; 1022 1151 -> 54 and 99,200 -> 8210; 1024
+// 1186 -> 19 and 187,000 -> 1602.
 // Mixed-radix stages with the plan as an argument took 24.4 us at 256 and 31.8 us at 1024
 // (index arithmetic on the one chain).
 #pragma once

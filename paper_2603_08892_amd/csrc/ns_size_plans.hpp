@@ -8,7 +8,7 @@
 // lines per block of the two z passes.
 //
 // How a plan was chosen: of all radix lists and thread counts that fit a tile of 128-byte
-// rows in 512 threads (y passes of FP32: 1024), the one of least estimated time,
+// rows in 512 threads (y passes: 1024), the one of least estimated time,
 // instructions of a thread (butterflies, twiddles, LDS exchanges, idle butterflies
 // included) times wavefronts per line over 1 - 1/(occupancy) with registers of about
 // 70 + 11.5 EPT (x of FP32), 90 + 24 EPT (x of FP64), 36 + 5 w EPT (y) and 40 + 13 w EPT (z), w = 1 (FP32) or 2 (FP64);
