@@ -202,13 +202,6 @@ struct FastCfg {
   using XLam = XL;
 };
 
-// The padding of a layout's x planes, known to be none at compile time on the grids without
-// streaming stores: the term costs registers where it is zero (f_xadj of 216 took 134 instead
-// of 127, one 512-thread tile a CU instead of two: 67 -> 98 us without and 147 -> 205 us with
-// operands, 216^3 C_t = 1).
-template <typename C>
-__device__ __forceinline__ int pad_of(int pad) { return stream_stores<typename C::T>(C::N) ? pad : 0; }
-
 // ------------------------------------------------------------------ x inverse
 // One active tile per block, all six fields.  Along an x line k_y and k_z are
 // fixed, so the x transform of omega_x = i (k_y u_z - k_z u_y) is
@@ -248,7 +241,7 @@ f_xinv(const Cx<typename C::T>* __restrict__ S, Lay ls, Cx<typename C::T>* __res
     phyz = phc[l];
   }
   const LineView<T, C::LP> lv{xb + l};
-  const uint32_t sbase = (uint32_t)(yi * ls.pitch + kz0) + l, sstep = (uint32_t)(N * ls.pitch + pad_of<C>(ls.pad));
+  const uint32_t sbase = (uint32_t)(yi * ls.pitch + kz0) + l, sstep = (uint32_t)(N * ls.pitch + ls.pad);
   [[maybe_unused]] const T kyf = T(ky), kzf = T(kz);
   Cx<T> ux[EPT], uy[EPT], uz[EPT], v[EPT];
   {
@@ -278,7 +271,7 @@ f_xinv(const Cx<typename C::T>* __restrict__ S, Lay ls, Cx<typename C::T>* __res
       uz[i] = cmul(uz[i], phi);
     }
   }
-  const uint32_t obase = (uint32_t)(yi * g.kzp + kz0) + l, ostep = (uint32_t)(N * g.kzp + pad_of<C>(g.pad));
+  const uint32_t obase = (uint32_t)(yi * g.kzp + kz0) + l, ostep = (uint32_t)(N * g.kzp + g.pad);
   auto store = [&](int f, const Cx<T>* v) {
     if (col) {
 #pragma unroll
@@ -335,7 +328,7 @@ f_ypass(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__
   for (int i = tid; i < N; i += C::L * TPL) tw[i] = twg[i];
   const bool col = kz < g.kzn;
   Cx<T>* base = W + f * g.wcomp;
-  const uint32_t rbase = (uint32_t)(x * (N * g.kzp + pad_of<C>(g.pad)) + kz0) + l;
+  const uint32_t rbase = (uint32_t)(x * (N * g.kzp + g.pad) + kz0) + l;
   const LineView<T, C::LP> lv{xb + l};
   Cx<T> v[EPT];
 #pragma unroll
@@ -388,7 +381,7 @@ f_ycurl(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__
   Cx<T>* const Wa = W + (grp ? 0 : 1) * g.wcomp;
   Cx<T>* const Wb = W + (grp ? 4 : 2) * g.wcomp;
   Cx<T>* const Wc = W + (grp ? 5 : 3) * g.wcomp;
-  const uint32_t rbase = (uint32_t)(x * (N * g.kzp + pad_of<C>(g.pad)) + kz0) + l;
+  const uint32_t rbase = (uint32_t)(x * (N * g.kzp + g.pad) + kz0) + l;
   const LineView<T, C::LP> lv{xb + l};
   Cx<T> va[EPT], vb[EPT], vc[EPT];
   {
@@ -472,7 +465,7 @@ f_zcross(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict_
   const int p = tid / TPL, t = tid % TPL;
   const uint32_t line = (uint32_t)blockIdx.x * P + p;
   const LineView<T, 1> lv{xb + p * LP};
-  const uint32_t lbase = line * (uint32_t)g.kzp + (line / N) * (uint32_t)pad_of<C>(g.pad);
+  const uint32_t lbase = line * (uint32_t)g.kzp + (line / N) * (uint32_t)g.pad;
   const uint32_t fbytes = (uint32_t)(g.wcomp * (long long)sizeof(Cx<T>));
   T fx[EPT], fy[EPT], fz[EPT];
   Cx<T> z[2][EPT];
@@ -632,14 +625,14 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
       const int p = F::out_at(t, c0 + j);
       const bool ok = line_kept && F::out_ok(t, c0 + j) && keep(kval(p, N));
       if constexpr (may0) {
-        const uint32_t ii0 = (uint32_t)((p * N + yi) * a.li0.pitch + p * pad_of<C>(a.li0.pad) + kz);
+        const uint32_t ii0 = (uint32_t)((p * N + yi) * a.li0.pitch + p * a.li0.pad + kz);
         if (need0) {
 #pragma unroll
           for (int c = 0; c < 3; ++c) s0v[buf][c][j] = ld_masked(a.in0 + c * a.li0.cs, ii0, ok);
         }
       }
       if constexpr (may1) {
-        const uint32_t ii1 = (uint32_t)((p * N + yi) * a.li1.pitch + p * pad_of<C>(a.li1.pad) + kz);
+        const uint32_t ii1 = (uint32_t)((p * N + yi) * a.li1.pitch + p * a.li1.pad + kz);
         if (need1) {
 #pragma unroll
           for (int c = 0; c < 3; ++c) s1v[buf][c][j] = ld_masked(a.in1 + c * a.li1.cs, ii1, ok);
@@ -660,7 +653,7 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
       }
     }
     const bool col = kz < g.kzn;
-    const uint32_t wbase = (uint32_t)(yi * g.kzp + kz0) + l, wstep = (uint32_t)(N * g.kzp + pad_of<C>(g.pad));
+    const uint32_t wbase = (uint32_t)(yi * g.kzp + kz0) + l, wstep = (uint32_t)(N * g.kzp + g.pad);
     // field f + 1 is loaded while field f is transformed
 #pragma unroll
     for (int i = 0; i < EPT; ++i) r[0][i] = ld_masked(W, (uint32_t)F::in_at(t, i) * wstep + wbase, col && F::in_ok(t, i));
@@ -692,7 +685,7 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
         if (!F::out_ok(t, i)) continue;  // no point in this register
         const int p = F::out_pos(t, i);
         const int kx = kval(p, N);
-        const uint32_t io0 = (uint32_t)((p * N + yi) * a.lo0.pitch + p * pad_of<C>(a.lo0.pad) + kz);
+        const uint32_t io0 = (uint32_t)((p * N + yi) * a.lo0.pitch + p * a.lo0.pad + kz);
         if (!(line_kept && keep(kx))) {
           // outside the retained set: zero in outputs that must be complete (full
           // mode, the caller's arrays); stage buffers are only read at retained modes
@@ -700,7 +693,7 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
             for (int c = 0; c < 3; ++c) st_off(a.out0 + c * a.lo0.cs, io0, cx(T(0), T(0)));
           continue;
         }
-        const uint32_t io1 = use1 ? (uint32_t)((p * N + yi) * a.lo1.pitch + p * pad_of<C>(a.lo1.pad) + kz) : 0u;
+        const uint32_t io1 = use1 ? (uint32_t)((p * N + yi) * a.lo1.pitch + p * a.lo1.pad + kz) : 0u;
         Cx<T> Fv[3] = {scale(r[0][i], inv_n3), scale(r[1][i], inv_n3), scale(r[2][i], inv_n3)};
         if (sh.on) {
           const Cx<T> phi = cmul(phx[p], phyz);
@@ -802,7 +795,7 @@ f_xfwd(Cx<typename C::T>* __restrict__ W, const Cx<typename C::T>* __restrict__ 
         uz[i] = cmul(uz[i], phi);
       }
     }
-    const uint32_t obase = (uint32_t)(yi * g.kzp + kz0) + l, ostep = (uint32_t)(N * g.kzp + pad_of<C>(g.pad));
+    const uint32_t obase = (uint32_t)(yi * g.kzp + kz0) + l, ostep = (uint32_t)(N * g.kzp + g.pad);
     auto store = [&](int f, const Cx<T>* v) {
       if (col) {
 #pragma unroll

@@ -13,6 +13,14 @@
 
 namespace ns {
 
+// The padding of a layout's x planes, known to be none at compile time on the grids without
+// streaming stores: the term costs registers where it is zero (f_xadj of 216 took 134 instead
+// of 127, one 512-thread tile a CU instead of two: 67 -> 98 us without and 147 -> 205 us with
+// operands, 216^3 C_t = 1).  In the forward passes it costs none, and they are no faster without
+// it (192^3, the third RK4 stage 29.5 with it, 30.2 us without).
+template <typename C>
+__device__ __forceinline__ int pad_of(int pad) { return stream_stores<typename C::T>(C::N) ? pad : 0; }
+
 // ------------------------------------------------------------------ lam x pass
 // lam_in = cA E_A(k) A + cB E_B(k) B on the retained modes, projected and shifted,
 // inverse x transforms into scratch fields 6, 7, 8 (tiles as f_xinv).
